@@ -76,6 +76,7 @@ struct ws_domain {
     bool vdirty;                   // pass argument tables must be rewritten
     int sy, pnt, solver;           // tuning: stencil rows per strip, PCR threads per system, reduced solver
     int syc;                       // stencil rows per strip in corrector passes (0: sy)
+    bool rows_set;                 // the heights above are the caller's (else short_rows() picks)
     size_t fstride;                // bytes between consecutive fields
     StencilArgs *vsa;              // pass argument tables (device), batch use only
     SolveArgs *vso;
@@ -938,9 +939,29 @@ static dim3 strips_for(const ws_domain *d, int sy, bool solo = false) {
     return dim3(solo ? ns : (ns + SWG - 1) / SWG, (d->g.ny + sy - 1) / sy);
 }
 
+// Strip height where the caller chose none (or the autotuner its shortest).
+// One wave walks a strip row by row, 1.4 us a row when it has its SIMD to
+// itself, after three warm-up rows; a shorter strip repeats more warm-up rows
+// but starts more waves.  So: the shortest of 1, 2, 4 and 8 rows that keeps
+// the launch within about three waves a SIMD (3200), 8 where none does.
+// Measured, us a step with rows of 32 / 8 / 4 / 2 / 1: 128 x 64 cells (192
+// waves at 1 row) 188 / 93 / 79 / 73 / 64; 601 x 601 (3005 at 2) 210 / 109 /
+// 97 / 95 / 100; 1024 x 512 (2176 at 4) 257 / 133 / 113 / 115 / 123;
+// 2048 x 1500 431 / 340 / 335 / 356 / 404.  Heights give the same bits.
+static long strip_waves(int nx, int ny, int sy) { return (long)((nx + SO - 1) / SO) * ((ny + sy - 1) / sy); }
+static constexpr long SHORT_WAVES = 3200;
+static int short_rows(int nx, int ny) {
+    int r = 1;
+    while (r < 8 && strip_waves(nx, ny, r) > SHORT_WAVES) r *= 2;
+    return r;
+}
+
 #define SY_SWITCH(K, sy, LAUNCH)                        \
     do {                                                \
-        if (sy == 8) LAUNCH(K<8>);                      \
+        if (sy == 1) LAUNCH(K<1>);                      \
+        else if (sy == 2) LAUNCH(K<2>);                 \
+        else if (sy == 4) LAUNCH(K<4>);                 \
+        else if (sy == 8) LAUNCH(K<8>);                 \
         else if (sy == 16) LAUNCH(K<16>);               \
         else if (sy == 24) LAUNCH(K<24>);               \
         else if (sy == 48) LAUNCH(K<48>);               \
@@ -1147,7 +1168,7 @@ static void launch_reduced(const ws_domain *d, hipStream_t st, const SolveArgs &
 static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st) {
     {
         ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
-        const int rows = sa.kind == 2 && d->syc ? d->syc : d->sy;
+        const int rows = !d->rows_set ? short_rows(d->g.nx, d->g.ny) : sa.kind == 2 && d->syc ? d->syc : d->sy;
         launch_stencil(d, rows, st, sa);
     }
     if (!so.nlsw) {  // NLSW: identity systems, nothing to solve
@@ -1288,7 +1309,24 @@ struct ws_batch {
     hipStream_t last = nullptr;
     int sy = SY, pnt = PCR_NT, solver = WS_SOLVE_PCR;  // tuning shared by all domains of the batch
     int syc = 0;                                        // corrector-pass stencil rows (0: sy)
+    bool rows_set = false;                              // the heights are the caller's (else batch_rows() picks)
+    int rp = SY, rc = SY;                               // heights the tables were built for
 };
+
+// Strip heights of the batch: the caller's or the autotuner's, else by the
+// rule of short_rows() on the waves of all its domains together.
+static void batch_rows(ws_batch *b, const std::vector<int> &order) {
+    b->rp = b->sy;
+    b->rc = b->syc ? b->syc : b->sy;
+    if (b->rows_set) return;
+    int r = 1;
+    for (; r < 8; r *= 2) {
+        long waves = 0;
+        for (int sl : order) waves += strip_waves(b->slots[sl]->g.nx, b->slots[sl]->g.ny, r);
+        if (waves <= SHORT_WAVES) break;
+    }
+    b->rp = b->rc = r;
+}
 
 static size_t batch_layout(int max, size_t *o_state, size_t *o_pre) {
     size_t a = align256(sizeof(BatchDesc) * (size_t)max);
@@ -1387,6 +1425,8 @@ static ws_status batch_upload(ws_batch *b) {
     std::vector<int> pre[5];
     for (int q = 0; q < 5; ++q) pre[q].assign(n + 1, 0);
     int maxK = 0, nred = 0;
+    const int rp0 = b->rp, rc0 = b->rc;
+    batch_rows(b, order);
     for (int k = 0; k < n; ++k) nred = std::max(nred, nred_of(b->slots[order[k]]));
     for (int k = 0; k < n; ++k) {
         ws_domain *d = b->slots[order[k]];
@@ -1399,7 +1439,7 @@ static ws_status batch_upload(ws_batch *b) {
             if (r != WS_OK) return r;
         }
         d->bidx = k;
-        desc[k] = make_desc(d, b->sy);
+        desc[k] = make_desc(d, b->rp);
         b->h_state[k].step = d->step;
         b->h_state[k].t = d->t;
         b->h_state[k].cur = d->cur;
@@ -1408,7 +1448,7 @@ static ws_status batch_upload(ws_batch *b) {
         const BatchDesc &D = desc[k];
         pre[0][k + 1] = pre[0][k] + D.sgx * D.sgy;
         pre[1][k + 1] = pre[1][k] + D.tgx * D.tgy;
-        const dim3 sgc = strips_for(d, b->syc ? b->syc : b->sy, true);  // the corrector's one-wave grid
+        const dim3 sgc = strips_for(d, b->rc, true);  // the corrector's one-wave grid
         pre[4][k + 1] = pre[4][k] + (int)(sgc.x * sgc.y);
         pre[2][k + 1] = pre[2][k] + (b->solver == WS_SOLVE_LU2                     ? solve2_waves(D.d.nx, D.d.ny)
                                      : b->solver == WS_SOLVE_LU && luw_waves(nred) ? luw_groups(D.d.nx, D.d.ny)
@@ -1424,7 +1464,7 @@ static ws_status batch_upload(ws_batch *b) {
         for (int q = 0; q < 5; ++q)
             HIPCHK(hipMemcpy(b->d_pre[q], pre[q].data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice));
     }
-    bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred;
+    bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0;
     for (int q = 0; q < 5; ++q) same = same && pre[q][n] == b->total[q];
     if (!same) batch_drop_graph(b);
     b->order = order;
@@ -1444,7 +1484,7 @@ static ws_status batch_step(ws_batch *b, hipStream_t st) {
     }
     for (int p = 0; p <= b->maxK; ++p) {
         // predictor pass: stencil_rows; corrector passes: their own height
-        const int q = p > 0 ? 4 : 0, rows = p > 0 && b->syc ? b->syc : b->sy;
+        const int q = p > 0 ? 4 : 0, rows = p > 0 ? b->rc : b->rp;
         const dim3 sg(b->total[q]), pg(b->total[2]);
 #define L4(KERN) hipLaunchKernelGGL(KERN, sg, dim3(p > 0 ? 64 : 64 * SWG), 0, st, b->d_desc, b->d_state, b->d_pre[q], n, p)
         if (p > 0) SY_SWITCH(kb_stencil_c, rows, L4);
@@ -1643,6 +1683,7 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
                     nred_of(d));
     d->sy = t->stencil_rows;
     d->syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
+    d->rows_set = true;
     d->pnt = t->pcr_threads;
     if (d->solver != t->solver) batch_touch(d);  // argument blocks carry the solve layout
     d->solver = t->solver;
@@ -1652,15 +1693,23 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
 extern "C" ws_status ws_batch_set_tuning(ws_batch *b, const ws_tuning *t) {
     if (!b || !tuning_ok(t)) return fail(WS_EINVAL, "ws_batch_set_tuning: bad tuning");
     const int syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
-    if (b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
+    if (!b->rows_set || b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
         b->sy = t->stencil_rows;
         b->syc = syc;
         b->pnt = t->pcr_threads;
         b->solver = t->solver;
+        b->rows_set = true;
         b->dirty = true;
         b->total[0] = -1;  // launch shapes change: the captured step is rebuilt
     }
     return WS_OK;
+}
+
+// The autotuner's choice, applied: its shortest height may be shortened.
+static ws_status set_tuned(ws_domain *d, const ws_tuning *t) {
+    const ws_status r = ws_set_tuning(d, t);
+    if (r == WS_OK && d->sy == 8 && d->syc == 0) d->rows_set = false;
+    return r;
 }
 
 static bool cache_lookup(const char *path, const ws_grid &g, ws_tuning *t) {
@@ -1691,7 +1740,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     ws_tuning best;
     std::memset(&best, 0, sizeof best);
     if (cache_lookup(cache_path, d->g, &best)) {
-        ws_status r = ws_set_tuning(d, &best);
+        ws_status r = set_tuned(d, &best);
         if (r == WS_OK) *out = best;
         return r;
     }
@@ -1827,7 +1876,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
             std::fclose(f);
         }
     }
-    ws_status r = ws_set_tuning(d, &best);
+    ws_status r = set_tuned(d, &best);
     if (r == WS_OK) *out = best;
     return r;
 }
@@ -1860,6 +1909,7 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     float best = 1e30f, best_c = 1e30f, tp[6], tc[6];
     for (int c = 0; c < 6; ++c) tp[c] = tc[c] = 1e30f;
     b->syc = 0;
+    b->rows_set = true;
     for (int c = 0; c < 6; ++c) {
         b->sy = rows[c];
         b->dirty = true;
@@ -1894,6 +1944,7 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     }
     b->sy = best_sy;
     b->syc = best_syc == best_sy ? 0 : best_syc;
+    if (b->sy == 8 && b->syc == 0) b->rows_set = false;  // the shortest candidate may be shortened
     b->dirty = true;
     if ((r = batch_upload(b)) != WS_OK) return r;
     const int n = (int)b->order.size();

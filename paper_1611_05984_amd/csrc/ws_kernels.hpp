@@ -134,9 +134,10 @@ __device__ __forceinline__ void st2(float *p, unsigned ob, float2 v) {
     *reinterpret_cast<float2 *>(reinterpret_cast<char *>(p) + ob) = v;
 }
 
-// Rows per stencil strip: a template parameter (8, 16, 24, 32, 48 or 64)
-// chosen per grid shape; taller strips spend less on the 4 warm-up rows,
-// shorter ones give more workgroups.
+// Rows per stencil strip: a template parameter (8, 16, 24, 32, 48 or 64, and
+// 1, 2 or 4 on grids too small to fill the chip otherwise) chosen per grid
+// shape; taller strips spend less on the 4 warm-up rows, shorter ones give
+// more workgroups.
 // The pass kind (A.kind) is a compile-time parameter: each kernel carries
 // no code, registers or branches for the other kinds.  SOLO: the workgroup
 // is one wave (one strip) instead of SWG side-by-side strips; the
@@ -206,8 +207,11 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
 
     // the corrector's row loop fully unrolled at 8 rows (no sliding-window
     // moves; corrector 208 -> 198 us at 4096^2); the predictor, with more
-    // live history values, is faster rolled
-#pragma unroll KIND == 2 && SYT <= 8 ? SYT + 4 : 1
+    // live history values, is faster rolled.  At 4 rows and fewer a wave has
+    // its SIMD nearly to itself and every kind is unrolled, so that rows need
+    // not wait for each other's loads (128 x 64 cells, 1 row: 61 -> 58 us a step)
+    constexpr int UNROLL = (KIND == 2 && SYT <= 8) || SYT <= 4 ? SYT + 4 : 1;
+#pragma unroll UNROLL
     for (int it = 0; it < SYT + 4; ++it) {
         const int r = j0 - 2 + it;
         e0 = e1; e1 = e2; e2 = e3; e3 = e4;
@@ -313,9 +317,10 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
                 const float inv_h = 1.41421356237f * h * frsq(h4 + fmaxf(h4, eps));
                 float fc = d.fcoef;
                 if (d.friction == FRIC_MANNING) fc = g * d.fcoef * d.fcoef * cbrtf(inv_h);
-                const float k = fc * fsqrt(p1 * p1 + q1 * q1) * inv_h * inv_h;
-                F -= k * p1;
-                G -= k * q1;
+                // explicit fused operations: the same bits in every strip height's code
+                const float k = fc * fsqrt(fmaf(p1, p1, q1 * q1)) * inv_h * inv_h;
+                F = fmaf(-k, p1, F);
+                G = fmaf(-k, q1, G);
             }
             if (out) {
                 const float dt = A.dt;
