@@ -321,7 +321,9 @@ ws_status ws_corrector_stats(const ws_domain *d, int32_t *last, int64_t *total, 
  * shorter strips (8 to 1 rows) where the grid or batch has too few waves to
  * fill the chip; ws_get_tuning then reports the nominal heights.  pcr_threads: threads
  * per reduced tridiagonal system in the partitioned solve (64, 128 or 256:
- * equations held per thread versus threads per barrier).  solver: the
+ * equations held per thread versus threads per barrier; no effect on grids
+ * of up to 16384 x 2048 cells, where the PCR strategies run a pass's solves as
+ * one kernel).  solver: the
  * reduced systems by PCR (WS_SOLVE_PCR) or by the Thomas algorithm with one
  * lane per system (WS_SOLVE_THOMAS: linear work, no barriers, a dependent
  * chain per lane) or by factors computed once per bathymetry and boundary

@@ -45,7 +45,9 @@ struct ws_domain {
     int nxp, nyp, pitch, zpitch, nu, nv;
     char *base;
     size_t bytes;
-    float *D, *Dnew;               // corner still-water depth (+ scratch for terrain edits)
+    float *D;                      // corner still-water depth
+    float *Dnew;                   // k_cells' field (depths of the cells, sponge factors); a terrain edit
+                                   // builds the new corners here first and refills it
     float *st[3][3];               // state of the step and two estimates (eta, P, Q)
     float *rx, *ry;                // U*, V* increments / eliminated segments
     float *S[3];                   // corrector bases
@@ -214,6 +216,19 @@ __device__ __forceinline__ float cell_Dc(const Dom &d, int i, int j) {
     return 0.25f * ((r0[i] + r0[i + 1]) + (r1[i] + r1[i + 1]));
 }
 
+// What the one-kernel solve reads of the cells: still-water depths, and in the
+// spare last column and row of that field the sponge factors of the rows and
+// of the columns.
+__global__ void k_cells(Dom d, float *out) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
+    if (i > d.nx || j > d.ny) return;
+    float v;
+    if (i < d.nx && j < d.ny) v = cell_Dc(d, i, j);
+    else if (j < d.ny) v = sponge_y(d, j);
+    else v = i < d.nx ? sponge_x(d, i) : 1.f;
+    out[(size_t)j * d.zpitch + i] = v;
+}
+
 // Lake at rest: eta = max(0, -D_cell) (surface at still water or on the bottom).
 __global__ void k_rest_state(Dom d, float *e, float *p, float *q) {
     int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
@@ -370,6 +385,11 @@ __global__ void k_side_depth(Dom d, int side, double *out) {
 }
 
 static dim3 cells_grid(int nx, int ny) { return dim3((nx + 255) / 256, ny); }
+// To be called whenever the bathymetry, a sponge or the time step (which
+// partially reflective sponges scale with) changed.
+static void refresh_cells(const ws_domain *d, hipStream_t st) {
+    hipLaunchKernelGGL(k_cells, cells_grid(d->g.nx + 1, d->g.ny + 1), dim3(256), 0, st, make_dom(d), d->Dnew);
+}
 
 // Largest change between two iterates of the state over the interior cells:
 // res[0] = max |eta1 - eta0|, res[1] = max(|P1 - P0|, |Q1 - Q0|), kept as
@@ -412,15 +432,7 @@ __global__ void k_sponge(Dom d, float *e, float *P, float *Q) {
     const float *r0 = d.D + (size_t)j * d.zpitch, *r1 = r0 + d.zpitch;
     const float Dc = 0.25f * ((r0[i] + r0[i + 1]) + (r1[i] + r1[i + 1]));
     if (!(Dc > 0.f)) return;
-    float gm = 1.f;
-    if (d.side[0].type == BC_SPONGE)
-        gm *= sponge_factor(sponge_gamma((i + 0.5f) * d.dx, d.side[0].width * d.dx), d.side[0].expo);
-    if (d.side[1].type == BC_SPONGE)
-        gm *= sponge_factor(sponge_gamma((d.nx - i - 0.5f) * d.dx, d.side[1].width * d.dx), d.side[1].expo);
-    if (d.side[2].type == BC_SPONGE)
-        gm *= sponge_factor(sponge_gamma((j + 0.5f) * d.dy, d.side[2].width * d.dy), d.side[2].expo);
-    if (d.side[3].type == BC_SPONGE)
-        gm *= sponge_factor(sponge_gamma((d.ny - j - 0.5f) * d.dy, d.side[3].width * d.dy), d.side[3].expo);
+    const float gm = sponge_x(d, i) * sponge_y(d, j);
     if (gm != 1.f) {
         const size_t o = (size_t)j * d.pitch + i;
         e[o] *= gm;
@@ -497,6 +509,7 @@ static ws_status domain_setup(ws_domain *d, const ws_grid *g, const float *z_cor
         Dom m = make_dom(d);
         hipLaunchKernelGGL(k_rest_state, cells_grid(g->nx, g->ny), dim3(256), 0, st, m, d->st[0][0],
                            d->st[0][1], d->st[0][2]);
+        refresh_cells(d, st);
         hipLaunchKernelGGL(k_check_dd, cells_grid(g->nx, g->ny), dim3(256), 0, st, m, d->health);
         e = hipGetLastError();
     }
@@ -683,6 +696,9 @@ extern "C" ws_status ws_set_boundary(ws_domain *d, int32_t side, const ws_bounda
     d->side_R[side] = R;
     d->side_depth[side] = dside;
     d->side_expo[side] = sponge_expo(d, side);
+    refresh_cells(d, 0);
+    HIPCHK(hipGetLastError());
+    HIPCHK(hipStreamSynchronize(0));
     if (nc > 0 && !(dref > 0.0)) return fail(WS_EINVAL, "ws_set_boundary: no positive depth along the side");
     std::vector<double> tab((size_t)MAXC * TABW, 0.0);
     const double g = d->g.g;
@@ -740,6 +756,8 @@ extern "C" ws_status ws_update_grid(ws_domain *d, const ws_grid *g, void *stream
         d->step = 0;
         for (int q = 0; q < 4; ++q)
             if (d->side_type[q] == WS_BC_SPONGE) d->side_expo[q] = sponge_expo(d, q);
+        refresh_cells(d, (hipStream_t)stream);
+        HIPCHK(hipGetLastError());
     }
     if (systems) d->lu_valid = false;
     batch_touch(d);
@@ -821,6 +839,7 @@ extern "C" ws_status ws_restore(ws_domain *d, const void *src_dev, size_t bytes,
     for (int sl = 0; sl < 3; ++sl)
         for (int f = 0; f < 5; ++f, p += fb) HIPCHK(hipMemcpyAsync(d->hist[sl][f], p, fb, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipMemcpyAsync(d->D, p, cb, hipMemcpyDeviceToDevice, st));
+    refresh_cells(d, st);
     HIPCHK(hipMemsetAsync(d->health, 0, sizeof(int), st));
     d->cur = 0;
     // history levels taken at another time step are not spaced by this one:
@@ -921,13 +940,18 @@ extern "C" ws_status ws_apply_edit(ws_domain *d, int32_t kind, double x0, double
     int flag = 0;
     HIPCHK(hipMemcpyAsync(&flag, d->scal, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (flag) return fail(WS_ENOTDD, "ws_apply_edit: terrain edit rejected (eq. 23 would lose diagonal dominance)");
+    if (flag) {
+        refresh_cells(d, st);
+        HIPCHK(hipGetLastError());
+        return fail(WS_ENOTDD, "ws_apply_edit: terrain edit rejected (eq. 23 would lose diagonal dominance)");
+    }
     std::swap(d->D, d->Dnew);
     d->lu_valid = false;
     batch_touch(d);
     m = make_dom(d);
     hipLaunchKernelGGL(k_edit_velocity, cells_grid(d->g.nx, d->g.ny), dim3(256), 0, st, m, d->Dnew, e, p, q);
     hipLaunchKernelGGL(k_shore_fix, cells_grid(d->g.nx, d->g.ny), dim3(256), 0, st, m, e, p, q);
+    refresh_cells(d, st);
     HIPCHK(hipGetLastError());
     return WS_OK;
 }
@@ -1042,11 +1066,33 @@ static void launch_pcrw_batch(int nred, dim3 pg, hipStream_t st, const BatchDesc
     else hipLaunchKernelGGL(kb_pcrw<8>, pg, dim3(64), 0, st, desc, state, pre, n, p);
 }
 
+static bool has_side(const ws_domain *d, int type) {
+    for (int q = 0; q < 4; ++q)
+        if (d->side_type[q] == type) return true;
+    return false;
+}
+static bool has_makers(const ws_domain *d) { return has_side(d, WS_BC_WAVES); }
+static bool has_sponges(const ws_domain *d) { return has_side(d, WS_BC_SPONGE); }
+
+// Whether the solves of a pass run as one kernel: the PCR strategies in the
+// dispersive model, on grids whose columns a workgroup can hold.
+static bool fused(const ws_domain *d) {
+    return (d->solver == WS_SOLVE_PCR || d->solver == WS_SOLVE_PCR_WAVE) && d->g.model == WS_BSNQ &&
+           fs_fits(d->g.nx, d->g.ny);
+}
+static void launch_solve(const ws_domain *d, hipStream_t st, const SolveArgs &so) {
+    const int T = fs_threads(d->g.nx, d->g.ny);
+    const dim3 grid(fs_row_groups(T, d->g.nx, d->g.ny) + fs_col_groups(T, d->g.nx, d->g.ny));
+    if (T <= FS_EARLY) hipLaunchKernelGGL(k_solve, grid, dim3(T), fs_lds(T), st, so);
+    else hipLaunchKernelGGL(k_solve_big, grid, dim3(T), fs_lds(T), st, so);
+}
+
 // One predictor or corrector pass: stencil, then the partitioned solves.
 // Arguments of pass p of a step.  cur: state buffer of the step's state;
 // sm: step index mod 3 (history slots); euler: one of the two start-up steps.
+// sponge: the last pass applies the sponge (the tolerance mode does it itself).
 static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int sm, int p, StencilArgs &sa,
-                      SolveArgs &so) {
+                      SolveArgs &so, bool sponge = true) {
     const ws_grid &g = d->g;
     const int K = euler ? 0 : g.n_corr;
     const int n0 = (sm + 2) % 3, n1 = (sm + 1) % 3, n2 = sm;
@@ -1088,30 +1134,35 @@ static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int
     std::memset(&so, 0, sizeof so);
     so.d = sa.d;
     so.rx = d->rx;
-    so.ry = d->ry;
+    so.Dc = d->Dnew;
+    so.fstride = (unsigned)d->fstride;
     so.redx = d->redx;
     so.redy = d->redy;
     so.solx = d->solx;
     so.soly = d->soly;
     so.eta = d->st[out][0];
     so.pout = d->st[out][1];
-    so.qout = d->st[out][2];
     so.pbase = d->st[a][1];
-    so.qbase = d->st[a][2];
+    so.eraw = so.eta;
     so.gh0 = d->ghost[0];
     so.gh1 = d->ghost[1];
     so.health = d->health;
     so.lux = d->lux;
     so.luy = d->luy;
     so.layout = (d->solver == WS_SOLVE_LU || d->solver == WS_SOLVE_LU2) ? 1 : 0;
-    so.sponge = p == K ? 1 : 0;
+    so.sponge = sponge && p == K ? 1 : 0;
     so.nlsw = g.model == WS_NLSW ? 1 : 0;
-}
-
-static bool has_makers(const ws_domain *d) {
-    for (int q = 0; q < 4; ++q)
-        if (d->side_type[q] == WS_BC_WAVES) return true;
-    return false;
+    sa.split = fused(d) ? 1 : 0;
+    if (sa.split) {
+        // the row half writes the damped surface while the column half reads
+        // the surface: the last pass of a domain with sponges leaves it in
+        // the first corrector base, which nothing reads any more
+        so.sponge = so.sponge && has_sponges(d);
+        if (so.sponge) {
+            sa.eout = d->S[0];
+            so.eraw = d->S[0];
+        }
+    }
 }
 
 static int solve_waves(const ws_domain *d) { return (d->g.ny + 63) / 64 + (d->g.nx + 63) / 64; }
@@ -1165,11 +1216,12 @@ static void launch_reduced(const ws_domain *d, hipStream_t st, const SolveArgs &
     }
 }
 
-static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st) {
-    {
-        ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
-        const int rows = !d->rows_set ? short_rows(d->g.nx, d->g.ny) : sa.kind == 2 && d->syc ? d->syc : d->sy;
-        launch_stencil(d, rows, st, sa);
+// The solves of a pass, from the increments to the new discharges.
+static void launch_solves(ws_domain *d, const SolveArgs &so, hipStream_t st) {
+    if (fused(d)) {
+        ProfScope p(d, st, WS_K_SOLVE);
+        launch_solve(d, st, so);
+        return;
     }
     if (!so.nlsw) {  // NLSW: identity systems, nothing to solve
         {
@@ -1185,6 +1237,15 @@ static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &
         ProfScope p(d, st, WS_K_EXPAND);
         hipLaunchKernelGGL(k_expand, tiles(d), dim3(NT), 0, st, so);
     }
+}
+
+static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st) {
+    {
+        ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
+        const int rows = !d->rows_set ? short_rows(d->g.nx, d->g.ny) : sa.kind == 2 && d->syc ? d->syc : d->sy;
+        launch_stencil(d, rows, st, sa);
+    }
+    launch_solves(d, so, st);
     HIPCHK(hipGetLastError());
     return WS_OK;
 }
@@ -1200,8 +1261,7 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
     const Dom m = make_dom(d);
     const bool makers = has_makers(d);
     const bool conv = d->tol_w > 0.0;
-    bool sponges = false;
-    for (int q = 0; q < 4; ++q) sponges = sponges || d->side_type[q] == WS_BC_SPONGE;
+    const bool sponges = has_sponges(d);
     unsigned *dres = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(d->health) + 128);
     for (int64_t n = 0; n < nsteps; ++n) {
         const int64_t s = d->step + 1;
@@ -1216,8 +1276,8 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
         StencilArgs sa;
         SolveArgs so;
         for (int p = 0; p <= K; ++p) {
-            pass_args(d, m, euler, d->cur, (int)(s % 3), p, sa, so);
-            if (conv) so.sponge = 0;  // applied once the count is known
+            // (with a tolerance the sponge is applied once the count is known)
+            pass_args(d, m, euler, d->cur, (int)(s % 3), p, sa, so, !conv);
             ws_status r = run_pass(d, sa, so, st);
             if (r != WS_OK) return r;
             if (conv && p >= 1) {
@@ -1296,13 +1356,15 @@ struct ws_batch {
     int max;
     BatchDesc *d_desc;
     BatchState *d_state;
-    int *d_pre[5];                       // prefix tables: stencil, tile, pcr, ghost, corrector-stencil workgroups
+    int *d_pre[6];                       // prefix tables: stencil, tile, pcr, ghost, corrector-stencil, one-kernel
+                                         // solve workgroups
     std::vector<ws_domain *> slots;      // attached domains by slot (nullptr = free)
     std::vector<int> order;              // slots in device table order
     std::vector<BatchState> h_state;     // host copy, device table order
     bool dirty = true;                   // tables must be rebuilt and uploaded
     bool stale = false;                  // device states ahead of the domains' host copies
-    int maxK = 0, nred = 0, total[5] = {0, 0, 0, 0, 0};
+    int maxK = 0, nred = 0, total[6] = {0, 0, 0, 0, 0, 0};
+    int fsT = 256;                       // threads of the one-kernel solve's workgroups
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t gstream = nullptr;
@@ -1334,7 +1396,7 @@ static size_t batch_layout(int max, size_t *o_state, size_t *o_pre) {
     size_t c = align256(sizeof(int) * (size_t)(max + 1));
     if (o_state) *o_state = a;
     if (o_pre) *o_pre = a + b;
-    return a + b + 5 * c;
+    return a + b + 6 * c;
 }
 
 static void batch_touch(ws_domain *d) {
@@ -1422,18 +1484,24 @@ static ws_status batch_upload(ws_batch *b) {
     const int n = (int)order.size();
     std::vector<BatchDesc> desc(n);
     b->h_state.assign(n, BatchState());
-    std::vector<int> pre[5];
-    for (int q = 0; q < 5; ++q) pre[q].assign(n + 1, 0);
+    std::vector<int> pre[6];
+    for (int q = 0; q < 6; ++q) pre[q].assign(n + 1, 0);
     int maxK = 0, nred = 0;
     const int rp0 = b->rp, rc0 = b->rc;
     batch_rows(b, order);
-    for (int k = 0; k < n; ++k) nred = std::max(nred, nred_of(b->slots[order[k]]));
+    int fsT = 256;
     for (int k = 0; k < n; ++k) {
         ws_domain *d = b->slots[order[k]];
         if (d->solver != b->solver) {  // the batch's solve strategy (and layout) applies
             d->solver = b->solver;
             d->vdirty = true;
         }
+        if (fused(d)) fsT = std::max(fsT, fs_threads(d->g.nx, d->g.ny));
+        else nred = std::max(nred, nred_of(d));
+    }
+    for (int k = 0; k < n; ++k) {
+        ws_domain *d = b->slots[order[k]];
+        const bool one = fused(d);
         if (d->vdirty) {
             ws_status r = write_vtab(d);
             if (r != WS_OK) return r;
@@ -1447,10 +1515,12 @@ static ws_status batch_upload(ws_batch *b) {
         b->h_state[k].health = 0;
         const BatchDesc &D = desc[k];
         pre[0][k + 1] = pre[0][k] + D.sgx * D.sgy;
-        pre[1][k + 1] = pre[1][k] + D.tgx * D.tgy;
+        pre[1][k + 1] = pre[1][k] + (one ? 0 : D.tgx * D.tgy);
+        pre[5][k + 1] = pre[5][k] + (one ? fs_row_groups(fsT, D.d.nx, D.d.ny) + fs_col_groups(fsT, D.d.nx, D.d.ny) : 0);
         const dim3 sgc = strips_for(d, b->rc, true);  // the corrector's one-wave grid
         pre[4][k + 1] = pre[4][k] + (int)(sgc.x * sgc.y);
-        pre[2][k + 1] = pre[2][k] + (b->solver == WS_SOLVE_LU2                     ? solve2_waves(D.d.nx, D.d.ny)
+        pre[2][k + 1] = pre[2][k] + (one                                           ? 0
+                                     : b->solver == WS_SOLVE_LU2                   ? solve2_waves(D.d.nx, D.d.ny)
                                      : b->solver == WS_SOLVE_LU && luw_waves(nred) ? luw_groups(D.d.nx, D.d.ny)
                                      : b->solver != WS_SOLVE_PCR && b->solver != WS_SOLVE_PCR_WAVE
                                          ? (D.d.ny + 63) / 64 + (D.d.nx + 63) / 64
@@ -1461,18 +1531,56 @@ static ws_status batch_upload(ws_batch *b) {
     if (n) {
         HIPCHK(hipMemcpy(b->d_desc, desc.data(), sizeof(BatchDesc) * n, hipMemcpyHostToDevice));
         HIPCHK(hipMemcpy(b->d_state, b->h_state.data(), sizeof(BatchState) * n, hipMemcpyHostToDevice));
-        for (int q = 0; q < 5; ++q)
+        for (int q = 0; q < 6; ++q)
             HIPCHK(hipMemcpy(b->d_pre[q], pre[q].data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice));
     }
-    bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0;
-    for (int q = 0; q < 5; ++q) same = same && pre[q][n] == b->total[q];
+    bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0 &&
+                fsT == b->fsT;
+    for (int q = 0; q < 6; ++q) same = same && pre[q][n] == b->total[q];
     if (!same) batch_drop_graph(b);
     b->order = order;
     b->maxK = maxK;
     b->nred = nred;
-    for (int q = 0; q < 5; ++q) b->total[q] = pre[q][n];
+    b->fsT = fsT;
+    for (int q = 0; q < 6; ++q) b->total[q] = pre[q][n];
     b->dirty = false;
     return WS_OK;
+}
+
+// The solves of pass p for every domain of the batch: one launch for the
+// domains on the one-kernel path, three for the others.
+static void batch_solves(ws_batch *b, hipStream_t st, int p) {
+    const int n = (int)b->order.size();
+    if (b->total[5] > 0) {
+        const int T = b->fsT;
+        if (T <= FS_EARLY)
+            hipLaunchKernelGGL(kb_solve, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5], n, p);
+        else
+            hipLaunchKernelGGL(kb_solve_big, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5],
+                               n, p);
+    }
+    if (b->total[1] == 0) return;
+    hipLaunchKernelGGL(kb_reduce, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, p);
+    const dim3 pg(b->total[2]);
+    const size_t shm = sizeof(float4) * b->nred;
+    if (b->solver == WS_SOLVE_LU2)
+        hipLaunchKernelGGL(kb_lu2_solve, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
+    else if (b->solver == WS_SOLVE_LU)
+        if (const int G = luw_waves(b->nred))
+            hipLaunchKernelGGL(kb_luw_solve, pg, dim3(64 * G), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
+        else
+            hipLaunchKernelGGL(kb_lu_solve, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
+    else if (b->solver == WS_SOLVE_THOMAS)
+        hipLaunchKernelGGL(kb_thomas, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
+    else if (b->solver == WS_SOLVE_PCR_WAVE && pcrw_fits(b->nred))  // (longer: the workgroup PCR, same bits)
+        launch_pcrw_batch(b->nred, pg, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
+    else
+        pcr_dispatch(b->pnt, pcr_epl(b->pnt, b->nred), [&](auto shape) {
+            using S = decltype(shape);
+            hipLaunchKernelGGL((kb_pcr<S::threads, S::epl>), pg, dim3(S::threads), shm, st, b->d_desc,
+                               b->d_state, b->d_pre[2], n, p);
+        });
+    hipLaunchKernelGGL(kb_expand, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, p);
 }
 
 // The launches of one step for every domain of the batch.
@@ -1485,7 +1593,7 @@ static ws_status batch_step(ws_batch *b, hipStream_t st) {
     for (int p = 0; p <= b->maxK; ++p) {
         // predictor pass: stencil_rows; corrector passes: their own height
         const int q = p > 0 ? 4 : 0, rows = p > 0 ? b->rc : b->rp;
-        const dim3 sg(b->total[q]), pg(b->total[2]);
+        const dim3 sg(b->total[q]);
 #define L4(KERN) hipLaunchKernelGGL(KERN, sg, dim3(p > 0 ? 64 : 64 * SWG), 0, st, b->d_desc, b->d_state, b->d_pre[q], n, p)
         if (p > 0) SY_SWITCH(kb_stencil_c, rows, L4);
         else {
@@ -1493,26 +1601,7 @@ static ws_status batch_step(ws_batch *b, hipStream_t st) {
             SY_SWITCH(kb_stencil_p, rows, L4);
         }
 #undef L4
-        hipLaunchKernelGGL(kb_reduce, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, p);
-        const size_t shm = sizeof(float4) * b->nred;
-        if (b->solver == WS_SOLVE_LU2)
-            hipLaunchKernelGGL(kb_lu2_solve, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-        else if (b->solver == WS_SOLVE_LU)
-            if (const int G = luw_waves(b->nred))
-                hipLaunchKernelGGL(kb_luw_solve, pg, dim3(64 * G), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-            else
-                hipLaunchKernelGGL(kb_lu_solve, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-        else if (b->solver == WS_SOLVE_THOMAS)
-            hipLaunchKernelGGL(kb_thomas, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-        else if (b->solver == WS_SOLVE_PCR_WAVE && pcrw_fits(b->nred))  // (longer: the workgroup PCR, same bits)
-            launch_pcrw_batch(b->nred, pg, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-        else
-            pcr_dispatch(b->pnt, pcr_epl(b->pnt, b->nred), [&](auto shape) {
-                using S = decltype(shape);
-                hipLaunchKernelGGL((kb_pcr<S::threads, S::epl>), pg, dim3(S::threads), shm, st, b->d_desc,
-                                   b->d_state, b->d_pre[2], n, p);
-            });
-        hipLaunchKernelGGL(kb_expand, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, p);
+        batch_solves(b, st, p);
     }
     hipLaunchKernelGGL(kb_finish, dim3((n + 255) / 256), dim3(256), 0, st, b->d_desc, b->d_state, n);
     HIPCHK(hipGetLastError());
@@ -1537,7 +1626,7 @@ extern "C" ws_status ws_batch_create(int32_t max_domains, void *workspace_dev, s
     b->d_desc = (BatchDesc *)base;
     b->d_state = (BatchState *)(base + o_state);
     const size_t c = align256(sizeof(int) * (size_t)(max_domains + 1));
-    for (int q = 0; q < 5; ++q) b->d_pre[q] = (int *)(base + o_pre + q * c);
+    for (int q = 0; q < 6; ++q) b->d_pre[q] = (int *)(base + o_pre + q * c);
     b->slots.assign(max_domains, nullptr);
     *out = b;
     return WS_OK;
@@ -1755,7 +1844,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     sa.kind = 2;
     so.eta = d->st[(d->cur + 2) % 3][0];
     so.pout = d->st[(d->cur + 2) % 3][1];
-    so.qout = d->st[(d->cur + 2) % 3][2];
+    so.eraw = so.eta;
     sa.eout = so.eta;
     so.sponge = 0;
     so.health = (int *)d->scal;  // keep the domain's health word out of the timing runs
@@ -1812,61 +1901,54 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
         best.stencil_rows = rows[cp];
         best.corrector_rows = rows[cc];
     }
-    // Reduced-system strategies, each timed as the reduction (whose layout and
-    // writes depend on the strategy: reduced equations, or right-hand sides
-    // only for the factored solves) followed by the solve, `reps` times.
-    const int nred = d->nu > d->nv ? d->nu : d->nv;
-    const int threads[3] = {64, 128, 256};
-    auto time_pairs = [&](const SolveArgs &sx, auto &&solve) -> float {
-        hipLaunchKernelGGL(k_reduce, tiles(d), dim3(NT), 0, st, sx);  // warm-up
-        solve();
+    // Solve strategies, each timed as all of a pass's solves (reduction,
+    // reduced systems and expansion, or the one kernel).  The factors of the
+    // factored solves are computed once and kept: they match the domain's
+    // current bathymetry and boundaries.
+    const int keep = d->solver, keep_pnt = d->pnt;
+    ws_status tr = WS_OK;
+    auto time_solves = [&](int solver, int pnt) {
+        if (tr != WS_OK) return;
+        d->solver = solver;
+        d->pnt = pnt;
+        if ((tr = ensure_factors(d, st)) != WS_OK) return;
+        SolveArgs sx = so;
+        sx.layout = factored(solver) ? 1 : 0;
+        launch_solves(d, sx, st);  // warm-up
         float total = 0.f;
         for (int k = 0; k < reps; ++k) {
             (void)hipEventRecord(e0, st);
-            hipLaunchKernelGGL(k_reduce, tiles(d), dim3(NT), 0, st, sx);
-            solve();
+            launch_solves(d, sx, st);
             (void)hipEventRecord(e1, st);
             (void)hipEventSynchronize(e1);
             float ms = 0.f;
             (void)hipEventElapsedTime(&ms, e0, e1);
             total += ms;
         }
-        return total;
-    };
-    so.layout = 0;
-    for (int c = 0; c < 3; ++c) {
-        const float ms = time_pairs(so, [&] { launch_pcr(threads[c], nred, d->g.ny + d->g.nx, st, so); });
-        if (ms < best_p) { best_p = ms; best.pcr_threads = threads[c]; best.solver = WS_SOLVE_PCR; }
-    }
-    if (pcrw_fits(nred)) {  // the wave form of PCR (same bits as the above)
-        const float ms = time_pairs(so, [&] { launch_pcrw(nred, d->g.ny + d->g.nx, st, so); });
-        if (ms < best_p) { best_p = ms; best.solver = WS_SOLVE_PCR_WAVE; }
-    }
-    {
-        const int waves = (d->g.ny + 63) / 64 + (d->g.nx + 63) / 64;  // the sweep overwrites the equations
-        const float ms = time_pairs(so, [&] { hipLaunchKernelGGL(k_thomas, dim3(waves), dim3(64), 0, st, so); });
-        if (ms < best_p) { best_p = ms; best.solver = WS_SOLVE_THOMAS; }
-    }
-    {
-        // factored solves: factors once (kept: they match the domain's current
-        // bathymetry and boundaries), then only the right-hand-side sweeps
-        const int keep = d->solver;
-        SolveArgs s1 = so;
-        s1.layout = 1;
-        for (int sv : {WS_SOLVE_LU, WS_SOLVE_LU2}) {
-            d->solver = sv;
-            ws_status r = ensure_factors(d, st);
-            if (r != WS_OK) {
-                d->solver = keep;
-                return r;
-            }
-            const float ms = time_pairs(s1, [&] { launch_reduced(d, st, s1); });
-            if (ms < best_p) { best_p = ms; best.solver = sv; }
+        if (total < best_p) {
+            best_p = total;
+            best.solver = solver;
+            if (solver == WS_SOLVE_PCR) best.pcr_threads = pnt;
         }
-        d->solver = keep;
+    };
+    const bool prof = d->prof_on;
+    d->prof_on = false;
+    d->solver = WS_SOLVE_PCR;
+    if (fused(d)) {
+        time_solves(WS_SOLVE_PCR, PCR_NT);  // the thread counts and the wave form are the same kernel
+    } else {
+        for (int c : {64, 128, 256}) time_solves(WS_SOLVE_PCR, c);
+        if (pcrw_fits(nred_of(d))) time_solves(WS_SOLVE_PCR_WAVE, keep_pnt);  // (same bits as the above)
     }
+    time_solves(WS_SOLVE_THOMAS, keep_pnt);
+    time_solves(WS_SOLVE_LU, keep_pnt);
+    time_solves(WS_SOLVE_LU2, keep_pnt);
+    d->solver = keep;
+    d->pnt = keep_pnt;
+    d->prof_on = prof;
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
+    if (tr != WS_OK) return tr;
     HIPCHK(hipGetLastError());
     if (cache_path) {
         FILE *f = std::fopen(cache_path, "a");
@@ -1903,7 +1985,7 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
         (void)hipEventElapsedTime(&ms, e0, e1);
         return ms;
     };
-    const int rows[6] = {8, 16, 24, 32, 48, 64}, threads[3] = {64, 128, 256};
+    const int rows[6] = {8, 16, 24, 32, 48, 64};
     int best_sy = b->sy, best_syc = b->syc, best_pnt = b->pnt, best_solver = WS_SOLVE_PCR;
     b->solver = WS_SOLVE_PCR;  // the PCR trials use the PCR prefix table
     float best = 1e30f, best_c = 1e30f, tp[6], tc[6];
@@ -1950,93 +2032,31 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     const int n = (int)b->order.size();
     best = 1e30f;
     if (n > 0) {
-        // each strategy timed as the reduction (its layout depends on the
-        // strategy) followed by the reduced solve
-        auto reduce = [&] {
-            hipLaunchKernelGGL(kb_reduce, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, 1);
+        // each strategy timed as all the solves of a corrector pass
+        auto time_solves = [&](int solver, int pnt) -> ws_status {
+            b->solver = solver;
+            b->pnt = pnt;
+            b->dirty = true;
+            ws_status q = batch_upload(b);
+            for (int sl : b->order)
+                if (q == WS_OK) q = ensure_factors(b->slots[sl], st);
+            if (q != WS_OK) return q;
+            const float ms = time_it([&] { batch_solves(b, st, 1); });
+            if (ms < best) {
+                best = ms;
+                best_solver = solver;
+                if (solver == WS_SOLVE_PCR) best_pnt = pnt;
+            }
+            return WS_OK;
         };
-        for (int c = 0; c < 3; ++c) {
-            const float ms = time_it([&] {
-                reduce();
-                const dim3 pg(b->total[2]);
-                const size_t shm = sizeof(float4) * b->nred;
-                pcr_dispatch(threads[c], pcr_epl(threads[c], b->nred), [&](auto shape) {
-                    using S = decltype(shape);
-                    hipLaunchKernelGGL((kb_pcr<S::threads, S::epl>), pg, dim3(S::threads), shm, st, b->d_desc,
-                                       b->d_state, b->d_pre[2], n, 1);
-                });
-            });
-            if (ms < best) { best = ms; best_pnt = threads[c]; }
+        const int pnt0 = b->pnt;
+        for (int c : {64, 128, 256}) {
+            if ((r = time_solves(WS_SOLVE_PCR, c)) != WS_OK) return r;
+            if (b->total[1] == 0) break;  // every domain on the one-kernel path: no thread counts
         }
-        if (pcrw_fits(b->nred)) {  // the wave form of PCR (the PCR prefix table)
-            const float ms = time_it([&] {
-                reduce();
-                launch_pcrw_batch(b->nred, dim3(b->total[2]), st, b->d_desc, b->d_state, b->d_pre[2], n, 1);
-            });
-            if (ms < best) { best = ms; best_solver = WS_SOLVE_PCR_WAVE; }
-        }
-        // lane-per-system Thomas (its prefix table differs: rebuilt for the trial)
-        b->solver = WS_SOLVE_THOMAS;  // trial
-        b->dirty = true;
-        if ((r = batch_upload(b)) != WS_OK) return r;
-        float total = 0.f;
-        for (int k = 0; k < 4; ++k) {
-            (void)hipEventRecord(e0, st);
-            reduce();
-            hipLaunchKernelGGL(kb_thomas, dim3(b->total[2]), dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, 1);
-            (void)hipEventRecord(e1, st);
-            (void)hipEventSynchronize(e1);
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            if (k > 0) total += ms;
-        }
-        if (total < best) {
-            best = total;
-            best_solver = WS_SOLVE_THOMAS;
-        }
-        // factored solve: argument blocks with the interleaved layout, factors
-        b->solver = WS_SOLVE_LU;  // trial
-        b->dirty = true;
-        if ((r = batch_upload(b)) != WS_OK) return r;
-        for (int sl : b->order)
-            if ((r = ensure_factors(b->slots[sl], st)) != WS_OK) return r;
-        total = 0.f;
-        for (int k = 0; k < 4; ++k) {
-            (void)hipEventRecord(e0, st);
-            reduce();
-            if (const int G = luw_waves(b->nred))
-                hipLaunchKernelGGL(kb_luw_solve, dim3(b->total[2]), dim3(64 * G), 0, st, b->d_desc, b->d_state,
-                                   b->d_pre[2], n, 1);
-            else
-                hipLaunchKernelGGL(kb_lu_solve, dim3(b->total[2]), dim3(64), 0, st, b->d_desc, b->d_state,
-                                   b->d_pre[2], n, 1);
-            (void)hipEventRecord(e1, st);
-            (void)hipEventSynchronize(e1);
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            if (k > 0) total += ms;
-        }
-        if (total < best) {
-            best = total;
-            best_solver = WS_SOLVE_LU;
-        }
-        b->solver = WS_SOLVE_LU2;  // trial
-        b->dirty = true;
-        if ((r = batch_upload(b)) != WS_OK) return r;
-        for (int sl : b->order)
-            if ((r = ensure_factors(b->slots[sl], st)) != WS_OK) return r;
-        total = 0.f;
-        for (int k = 0; k < 4; ++k) {
-            (void)hipEventRecord(e0, st);
-            reduce();
-            hipLaunchKernelGGL(kb_lu2_solve, dim3(b->total[2]), dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, 1);
-            (void)hipEventRecord(e1, st);
-            (void)hipEventSynchronize(e1);
-            float ms = 0.f;
-            (void)hipEventElapsedTime(&ms, e0, e1);
-            if (k > 0) total += ms;
-        }
-        if (total < best) best_solver = WS_SOLVE_LU2;
+        if (b->total[1] > 0 && pcrw_fits(b->nred) && (r = time_solves(WS_SOLVE_PCR_WAVE, pnt0)) != WS_OK) return r;
+        for (int sv : {WS_SOLVE_THOMAS, WS_SOLVE_LU, WS_SOLVE_LU2})
+            if ((r = time_solves(sv, pnt0)) != WS_OK) return r;
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -16,7 +16,7 @@
 // their Euler start-up skip the corrector passes.  A last tiny kernel
 // advances every domain's state.
 #pragma once
-#include "ws_kernels.hpp"
+#include "ws_solve.hpp"
 
 namespace ws {
 
@@ -191,6 +191,32 @@ __global__ __launch_bounds__(NTB) void kb_expand(const BatchDesc *__restrict__ d
     const int local = b - prefix[dm];
     const SolveArgs A = load_params(D.so + v);
     expand_body<NTB>(A, s, local % D.tgx, local / D.tgx);
+}
+
+// The one-kernel solve over a batch, with the workgroup size the largest of
+// its domains needs.  Domains on the three-kernel path have no workgroups
+// here, and the others none in those kernels.
+template <bool EARLY>
+__device__ __forceinline__ void kb_solve_body(const BatchDesc *descs, const BatchState *states, const int *prefix,
+                                              int ndom, int p, float *lds) {
+    const int b = blockIdx.x, dm = find_dom(prefix, ndom, b);
+    const BatchDesc &D = descs[dm];
+    const int v = variant(D, states[dm], p);
+    if (v < 0) return;
+    const SolveArgs A = load_params(D.so + v);
+    solve_body<EARLY>(A, lds, b - prefix[dm]);
+}
+__global__ __launch_bounds__(FS_EARLY) __attribute__((amdgpu_waves_per_eu(2))) void kb_solve(
+    const BatchDesc *__restrict__ descs, const BatchState *__restrict__ states, const int *__restrict__ prefix,
+    int ndom, int p) {
+    extern __shared__ __align__(16) float fs_buf[];
+    kb_solve_body<true>(descs, states, prefix, ndom, p, fs_buf);
+}
+__global__ __launch_bounds__(1024) void kb_solve_big(const BatchDesc *__restrict__ descs,
+                                                     const BatchState *__restrict__ states,
+                                                     const int *__restrict__ prefix, int ndom, int p) {
+    extern __shared__ __align__(16) float fs_buf[];
+    kb_solve_body<false>(descs, states, prefix, ndom, p, fs_buf);
 }
 
 // Reduced systems by lane-per-system Thomas: workgroup (one wave) b - prefix

@@ -276,12 +276,26 @@ __device__ __forceinline__ void tri_coef(const Dom &d, TriK k, float dep, float 
     tri_coef_bsnq(k, dep, dd, A, B, C);
 }
 
-__device__ __forceinline__ float sponge_gamma(float dist, float Ls) {
-    return dist >= Ls ? 1.f : 0.5f * (1.f + cosf(3.14159265358979f * (Ls - dist) / Ls));
+// Sponge layers (eq. 30): gamma = (1 + cos(pi (Ls - dist) / Ls)) / 2 within Ls
+// of the side; a partially reflective layer damps by gamma^s (s = 1: the
+// layer of eq. 30).  The factor of a cell is that of its column (west and
+// east layers) times that of its row (south and north).  Contraction is off,
+// so that every kernel rounds it alike.
+__device__ inline float sponge_side(const SideDev &s, float dist, float Ls) {
+#pragma clang fp contract(off)
+    if (s.type != BC_SPONGE || dist >= Ls) return 1.f;
+    const float gamma = 0.5f * (1.f + cospif((Ls - dist) / Ls));
+    return s.expo == 1.f ? gamma : s.expo == 0.f ? 1.f : powf(gamma, s.expo);
 }
-// A partially reflective layer damps by gamma^s (s = 1: the layer of eq. 30).
-__device__ __forceinline__ float sponge_factor(float gamma, float s) {
-    return s == 1.f ? gamma : s == 0.f ? 1.f : powf(gamma, s);
+__device__ inline float sponge_x(const Dom &d, int i) {
+#pragma clang fp contract(off)
+    return sponge_side(d.side[0], ((float)i + 0.5f) * d.dx, (float)d.side[0].width * d.dx) *
+           sponge_side(d.side[1], ((float)(d.nx - i) - 0.5f) * d.dx, (float)d.side[1].width * d.dx);
+}
+__device__ inline float sponge_y(const Dom &d, int j) {
+#pragma clang fp contract(off)
+    return sponge_side(d.side[2], ((float)j + 0.5f) * d.dy, (float)d.side[2].width * d.dy) *
+           sponge_side(d.side[3], ((float)(d.ny - j) - 0.5f) * d.dy, (float)d.side[3].width * d.dy);
 }
 
 }  // namespace ws

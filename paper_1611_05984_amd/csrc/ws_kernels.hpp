@@ -1,6 +1,7 @@
 // ws_kernels.hpp -- the gfx950 kernels of one predictor/corrector pass.
 //
-// A pass is four launches:
+// A pass is the stencil and one launch of solves (ws_solve.hpp) where a
+// workgroup can hold the grid's columns, else four launches:
 //   k_stencil_{e,p,c}  (Euler predictor, AB3 predictor, AM4 corrector)
 //              column-streaming: one wave owns a strip of 64 columns (62 of
 //              them output) and walks 8-64 rows (tuned) with a sliding
@@ -41,7 +42,7 @@ struct StencilArgs {
     Dom d;
     const float *in;     // estimate read (the state itself for the predictor): eta, P, Q
     float *eout;         // new surface
-    float *rxy;          // U* - U*^n, V* - V*^n, packed per cell
+    float *rxy;          // U* - U*^n, V* - V*^n, packed per cell (or two fields: split)
     float *h0;           // history level n (predictors write it): (E, F, G), (F*, G*) packed
     const float *h1;     // level n-1
     const float *h2;     // level n-2
@@ -54,6 +55,7 @@ struct StencilArgs {
     float dt, x0, x1, x2;  // step, F* extrapolation weights
     int kind;            // 0 Euler predictor, 1 AB3 predictor, 2 AM4 corrector
     int write_S;
+    int split;           // the increments as two fields (one-kernel solve) instead of packed pairs
 };
 
 __device__ __forceinline__ float dcell4(float a, float b, float c, float d) {
@@ -350,7 +352,12 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
                     st2(A.h0, F3b + 2u * o, make_float2(Fs, Gs));
                 }
                 sto(A.eout, o, fmaxf(en, -Dc));
-                st2(A.rxy, 2u * o, make_float2(U, V));
+                if (A.split) {
+                    sto(A.rxy, o, U);
+                    sto(A.rxy, o + F1, V);
+                } else {
+                    st2(A.rxy, 2u * o, make_float2(U, V));
+                }
             }
         }
         hiy_prev = hiy;
@@ -401,8 +408,9 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 // ------------------------------------------------------------- solver parts
 struct SolveArgs {
     Dom d;
-    float *rx, *ry;            // right-hand sides (read by the reduction and the expansion):
-                               // the pair packed per cell from rx on (ry: its second field)
+    float *rx;                 // right-hand sides: pairs packed per cell (reduction and
+                               // expansion), or two fields (one-kernel solve)
+    const float *Dc;           // cell still-water depth (unclamped), rows of zpitch (one-kernel solve)
     float4 *redx, *redy;       // reduced equations (sub, diag, super, rhs) per unknown
     float *solx, *soly;        // reduced solutions
     // layout 1 (factored solve): the reduced right-hand sides (in the memory of
@@ -412,11 +420,13 @@ struct SolveArgs {
     // super-diagonals.
     const float *lux, *luy;
     int layout;
-    float *eta, *pout, *qout;  // new surface (read; sponge writes it), new P, Q
-    const float *pbase, *qbase;  // P^n, Q^n of the step
+    float *eta, *pout;         // new surface (read; sponge writes it), new P (Q one field on)
+    const float *pbase;        // P^n of the step (Q^n one field on)
+    const float *eraw;         // new surface before the sponge (one-kernel solve)
     const float *gh0, *gh1;    // wave-maker ghosts at t^n and t^{n+1}
     int *health;
     int sponge;
+    unsigned fstride;  // bytes between consecutive fields
     int nlsw;  // NLSW: the systems are the identity, the increments in rx, ry are final
 };
 
@@ -1254,7 +1264,7 @@ __device__ __forceinline__ void expand_body(const SolveArgs &A, SolveTile &s, in
         const bool in = i < d.nx && j < d.ny;
         pre_e[m] = in ? A.eta[o] : 0.f;
         pre_p[m] = in ? A.pbase[o] : 0.f;
-        pre_q[m] = in ? A.qbase[o] : 0.f;
+        pre_q[m] = in ? ldp(A.pbase, A.fstride)[o] : 0.f;
     }
     stage_tile<T>(A, s, i0, j0);
     if (A.nlsw) {
@@ -1317,15 +1327,7 @@ __device__ __forceinline__ void expand_body(const SolveArgs &A, SolveTile &s, in
             Q *= f;
         }
         if (A.sponge && Dc > 0.f) {
-            float gm = 1.f;
-            if (d.side[0].type == BC_SPONGE)
-                gm *= sponge_factor(sponge_gamma((i + 0.5f) * d.dx, d.side[0].width * d.dx), d.side[0].expo);
-            if (d.side[1].type == BC_SPONGE)
-                gm *= sponge_factor(sponge_gamma((d.nx - i - 0.5f) * d.dx, d.side[1].width * d.dx), d.side[1].expo);
-            if (d.side[2].type == BC_SPONGE)
-                gm *= sponge_factor(sponge_gamma((j + 0.5f) * d.dy, d.side[2].width * d.dy), d.side[2].expo);
-            if (d.side[3].type == BC_SPONGE)
-                gm *= sponge_factor(sponge_gamma((d.ny - j - 0.5f) * d.dy, d.side[3].width * d.dy), d.side[3].expo);
+            const float gm = sponge_x(d, i) * sponge_y(d, j);
             if (gm != 1.f) {
                 e *= gm;
                 P *= gm;
@@ -1335,7 +1337,7 @@ __device__ __forceinline__ void expand_body(const SolveArgs &A, SolveTile &s, in
         }
         bad |= !(isfinite(P) && isfinite(Q) && isfinite(e));
         A.pout[o] = P;
-        A.qout[o] = Q;
+        const_cast<float *>(ldp(A.pout, A.fstride))[o] = Q;
     }
     // one atomic per wave: a non-finite state must not serialize every thread
     // of the launch on the health word

@@ -1,0 +1,442 @@
+// ws_solve.hpp -- the implicit solves of one pass in a single launch: every
+// workgroup takes whole rows (eq. 21) or whole columns (eq. 22) from the
+// increments to the new discharges, with nothing in memory in between.
+//
+// A lane owns one segment of FM cells in registers: coefficients of eq. 23
+// from the cell depths, elimination of the segment's interior in favour of
+// its first and last unknowns (the partition method, as seg_eliminate), one
+// equation per segment for the last unknowns alone, parallel cyclic reduction
+// of those equations across the lanes through LDS (one barrier a level, two
+// buffers), back substitution, and the epilogue (P = P^n + dP, shoreline fix,
+// sponge).  The elimination and its reciprocals are done once, not once in a
+// reduction and again in an expansion, and the increments, the depth and the
+// equations cross memory once: 10 words a cell (U*, V* increments, depth and
+// surface twice, P^n, Q^n, P, Q) against 12.75 in three kernels, and one
+// launch (4 to 5 us each at the smallest sizes) instead of three.
+// Row workgroups read whole rows 16 bytes a lane and hand the cells to the
+// owning lanes through LDS (segments padded to FMP floats: conflict-free
+// 16-byte accesses); column workgroups read C consecutive columns of each
+// row, C lanes a run, straight into the owning lanes' registers.
+// us a pass's solves, three kernels (reduction, best PCR, expansion) / one:
+// 128 x 64 cells 17.5 / 9.8, 1024 x 512 20 / 11.7, 1024 x 1024 25 / 17, 2048 x
+// 1500 58 / 39.  Bound by latency up to about a million cells (4 us of launch,
+// two trips to memory), above by the columns' 32-byte runs: a workgroup pulls
+// whole 128-byte lines through its CU's 64 bytes a clock.
+#pragma once
+#include "ws_kernels.hpp"
+
+namespace ws {
+
+constexpr int FM = 16;    // cells a lane owns
+constexpr int FMP = 20;   // their LDS stride (floats)
+constexpr int FS_MAXSEG = 128;  // column segments a workgroup takes at most (8 columns a run: 2048 rows)
+
+// Threads of a workgroup (T, whole waves): 8 columns a run, at least one
+// whole row, at least 256.  Runs of 16 columns (64 bytes) halve the lines a
+// column workgroup shares with its neighbours, but also the workgroups: us a
+// solve at 16 / 8 / 4 columns: 601 x 601 14.2 / 12.6 / 12.8, 1024 x 512 12.3 /
+// 11.7 / 11.9, 1024 x 1024 20.0 / 17.3 / 18, 2048 x 1500 (8) 39.6 / (4) 41.
+__host__ __device__ constexpr int fs_segs(int n) { return (n + FM - 1) / FM; }
+inline int fs_threads(int nx, int ny) {
+    const int need = 8 * fs_segs(ny), m = need > fs_segs(nx) ? need : fs_segs(nx);
+    return m <= 256 ? 256 : (m + 63) / 64 * 64;
+}
+inline bool fs_fits(int nx, int ny) { return fs_segs(ny) <= FS_MAXSEG && fs_segs(nx) <= 1024; }
+// Rows of a row workgroup, columns of a column workgroup (a power of two, at
+// most 64), workgroups of each (rows padded to the 8 XCDs).
+__host__ __device__ inline int fs_rows(int T, int nx) { return T / fs_segs(nx); }
+__host__ __device__ inline int fs_cols(int T, int ny) {
+    const int c = T / fs_segs(ny);
+    return c >= 64 ? 64 : c >= 32 ? 32 : c >= 16 ? 16 : 8;
+}
+__host__ __device__ inline int fs_row_groups(int T, int nx, int ny) {
+    const int r = fs_rows(T, nx);
+    return ((ny + r - 1) / r + 7) / 8 * 8;
+}
+__host__ __device__ inline int fs_col_groups(int T, int nx, int ny) {
+    const int c = fs_cols(T, ny);
+    return (nx + c - 1) / c;
+}
+constexpr size_t fs_lds(int T) { return (size_t)T * FMP * sizeof(float); }
+
+// One segment: cells i0 .. i0 + FM - 1 of a line of n cells, dep[k] the
+// still-water depth of cell i0 + k - 1, r the right-hand sides.  Coefficients
+// of eq. 23, and the elimination of the interior: afterwards row k reads
+// a_k x_first + x_k / b_k + c_k x_last = r_k (b holds reciprocals, 1 <= k <=
+// FM - 2); f: x_first = f.z - f.x x_{-1} - f.y x_last; l: l.x x_first +
+// l.y x_last + l.z x_{+1} = l.w.  The line's ends fold as in seg_coefs (glo,
+// ghi: the maker's discharge change, 0 behind a wall), by selects: a branch
+// had the compiler copy all four arrays.  Cells past the end need not be
+// identity rows: no cell of the line refers to them.  Coefficients and
+// forward elimination go cell by cell, with a scheduling fence every few, so
+// that the depths die as the rows are born (64 live values, not 82).
+__device__ __forceinline__ void fs_eliminate(TriK tk, int i0, int n, bool lo_wall, bool hi_wall, float glo, float ghi,
+                                             const float (&dep)[FM + 2], float (&a)[FM], float (&b)[FM],
+                                             float (&c)[FM], float (&r)[FM], float3 &f, float4 &l) {
+#pragma clang fp contract(off)
+    const int kl = n - 1 - i0;  // the line's last cell
+    const float hw = hi_wall ? 1.f : 0.f;
+#pragma unroll
+    for (int k = 0; k < FM; ++k) {
+        const float dc = dep[k + 1], dd = dep[k + 2] - dep[k];
+        const float al = tk.kal * (dc * dc), be = tk.kbe * (dc * dd);
+        float ak = be - al, bk = fmaf(2.f, al, 1.f), ck = -be - al;
+        const float cw = k == kl ? ck : 0.f;
+        bk = fmaf(-cw, hw, bk);
+        r[k] = fmaf(-cw, ghi, r[k]);
+        ck -= cw;
+        if (k == 0) {
+            const float aw = i0 == 0 ? ak : 0.f;
+            bk = lo_wall ? bk - aw : bk;
+            r[0] = fmaf(-aw, glo, r[0]);
+            ak -= aw;
+        }
+        if (k == 1) bk = frcp(bk);
+        if (k >= 2 && k <= FM - 2) {
+            const float m = ak * b[k - 1];
+            ak = -m * a[k - 1];
+            bk = frcp(fmaf(-m, c[k - 1], bk));
+            r[k] = fmaf(-m, r[k - 1], r[k]);
+        }
+        if (k == FM - 1) {
+            const float m = ak * b[k - 1];
+            l = make_float4(-m * a[k - 1], fmaf(-m, c[k - 1], bk), ck, fmaf(-m, r[k - 1], r[k]));
+        } else {
+            a[k] = ak;
+            b[k] = bk;
+            c[k] = ck;
+        }
+        if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int k = FM - 3; k >= 1; --k) {
+        const float m = c[k] * b[k + 1];
+        a[k] = fmaf(-m, a[k + 1], a[k]);
+        c[k] = -m * c[k + 1];
+        r[k] = fmaf(-m, r[k + 1], r[k]);
+    }
+    const float m = c[0] * b[1];
+    const float inv = frcp(fmaf(-m, a[1], b[0]));
+    f = make_float3(a[0] * inv, -m * c[1] * inv, fmaf(-m, r[1], r[0]) * inv);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// The segments' equations across the lanes of a workgroup: segment s of nseg
+// of a line, its neighbours `str` threads away.  Returns x_first and x_last.
+// buf: 6 T floats.  Every thread of the workgroup calls it (nseg is uniform).
+__device__ __forceinline__ float2 fs_reduced(float3 f, float4 l, int s, int nseg, int str, float *buf) {
+#pragma clang fp contract(off)
+    const int t = threadIdx.x, T = blockDim.x;
+    float *cur = buf, *nxt = buf + 3 * T;
+    auto put = [&](float *p, float x, float y, float z) {
+        p[t] = x;
+        p[T + t] = y;
+        p[2 * T + t] = z;
+    };
+    auto get = [&](const float *p, int s2, int t2) {  // zeros past the line's ends
+        const bool in = s2 >= 0 && s2 < nseg;
+        const int q = in ? t2 : t;
+        return make_float3(in ? p[q] : 0.f, in ? p[T + q] : 0.f, in ? p[2 * T + q] : 0.f);
+    };
+    put(cur, f.x, f.y, f.z);
+    __syncthreads();
+    const float3 n = get(cur, s + 1, t + str);  // first unknown of the next segment
+    // l.x x_first + l.y x + l.z x_next_first = l.w with both firsts replaced
+    float d = frcp(fmaf(-l.x, f.y, fmaf(-l.z, n.x, l.y)));
+    float ea = -l.x * f.x * d, ec = -l.z * n.y * d, er = fmaf(-l.x, f.z, fmaf(-l.z, n.z, l.w)) * d;
+    for (int st = 1; st < nseg; st <<= 1) {
+        float *p = cur;
+        cur = nxt;
+        nxt = p;
+        put(cur, ea, ec, er);
+        __syncthreads();
+        const float3 m = get(cur, s - st, t - st * str), q = get(cur, s + st, t + st * str);
+        d = frcp(fmaf(-ea, m.y, fmaf(-ec, q.x, 1.f)));
+        er = fmaf(-ea, m.z, fmaf(-ec, q.z, er)) * d;
+        ea = -ea * m.x * d;
+        ec = -ec * q.y * d;
+    }
+    nxt[t] = er;
+    __syncthreads();
+    const float xm = s > 0 ? nxt[t - str] : 0.f;  // last unknown of the segment before
+    return make_float2(fmaf(-f.x, xm, fmaf(-f.y, er, f.z)), er);
+}
+
+__device__ __forceinline__ void fs_back(const float (&a)[FM], const float (&b)[FM], const float (&c)[FM],
+                                        float (&r)[FM], float2 x) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int k = 1; k <= FM - 2; ++k) r[k] = fmaf(-a[k], x.x, fmaf(-c[k], x.y, r[k])) * b[k];
+    r[0] = x.x;
+    r[FM - 1] = x.y;
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Shoreline fix of one discharge: h times the desingularized velocity.
+__device__ __forceinline__ float shore(float m, float e, float Dc, float eps) {
+    const float h = e + Dc, h2 = h * h;
+    return h2 * h2 < eps ? m * (1.41421356237f * h2 * frsq(fmaf(h2, h2, eps))) : m;
+}
+
+// Depth of the ghost cell behind a wave-maker side: the side's corners held.
+__device__ __forceinline__ float held_depth(const float *D, size_t c0, size_t c1) {
+    return fmaxf(0.25f * ((D[c0] + D[c0]) + (D[c1] + D[c1])), 0.f);
+}
+
+template <bool EARLY>
+__device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T, int g) {
+#pragma clang fp contract(off)
+    const Dom &d = A.d;
+    const int nseg = fs_segs(d.nx), R = fs_rows(T, d.nx);
+    const int t = threadIdx.x, row = t / nseg, s = t - row * nseg, j = g * R + row;
+    const bool live = row < R && j < d.ny;
+    const size_t o = (size_t)(live ? j : 0) * d.pitch, oz = (size_t)(live ? j : 0) * d.zpitch;
+    // coalesced: thread (row, s) moves 16 bytes at cells 4 (s + m nseg)
+    float4 vr[4], vd[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int q = 4 * (s + m * nseg);
+        vr[m] = live ? *reinterpret_cast<const float4 *>(A.rx + o + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + oz + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        // padding past the row's end is never written: whatever it holds must not spread
+        vr[m].x = q < d.nx ? vr[m].x : 0.f;
+        vr[m].y = q + 1 < d.nx ? vr[m].y : 0.f;
+        vr[m].z = q + 2 < d.nx ? vr[m].z : 0.f;
+        vr[m].w = q + 3 < d.nx ? vr[m].w : 0.f;
+    }
+    const int i0 = s * FM;
+    float glo = 0.f, ghi = 0.f, dlo = 0.f, dhi = 0.f;  // maker changes and ghost depths of the row's ends
+    if (live && s == 0 && !is_wall(d, 0)) {
+        glo = A.gh1[ghost_index(d, 0, 0, j + 2) + 1] - A.gh0[ghost_index(d, 0, 0, j + 2) + 1];
+        dlo = held_depth(d.D, oz, oz + d.zpitch);
+    }
+    if (live && s == nseg - 1 && !is_wall(d, 1)) {
+        ghi = A.gh1[ghost_index(d, 1, 0, j + 2) + 1] - A.gh0[ghost_index(d, 1, 0, j + 2) + 1];
+        dhi = held_depth(d.D, oz + d.nx, oz + d.zpitch + d.nx);
+    }
+    float *mine = lds + (size_t)(row < R ? row * nseg : 0) * FMP;  // the row's segments
+    auto put4 = [&](const float4 (&v)[4]) {
+        if (row < R)
+#pragma unroll
+            for (int m = 0; m < 4; ++m) {
+                const int q = s + m * nseg;
+                *reinterpret_cast<float4 *>(mine + (q >> 2) * FMP + 4 * (q & 3)) = v[m];
+            }
+    };
+    float dep[FM + 2], r[FM], a[FM], b[FM], c[FM];
+    put4(vd);
+    __syncthreads();
+    const float *seg = mine + (row < R ? s : 0) * FMP;
+#pragma unroll
+    for (int k = 0; k < FM; k += 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(seg + k);
+        dep[k + 1] = fmaxf(v.x, 0.f);
+        dep[k + 2] = fmaxf(v.y, 0.f);
+        dep[k + 3] = fmaxf(v.z, 0.f);
+        dep[k + 4] = fmaxf(v.w, 0.f);
+    }
+    dep[0] = s > 0 && row < R ? fmaxf(seg[FM - 1 - FMP], 0.f) : is_wall(d, 0) ? dep[1] : dlo;
+    dep[FM + 1] = s < nseg - 1 && row < R ? fmaxf(seg[FMP], 0.f) : 0.f;
+    __syncthreads();
+    put4(vr);
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < FM; k += 4) {
+        const float4 v = *reinterpret_cast<const float4 *>(seg + k);
+        r[k] = v.x;
+        r[k + 1] = v.y;
+        r[k + 2] = v.z;
+        r[k + 3] = v.w;
+    }
+    {   // the ghost past the row's last cell: mirrored, or held behind a maker
+        const int kl = d.nx - 1 - i0;
+        const bool wall = is_wall(d, 1);
+#pragma unroll
+        for (int k = 0; k < FM; ++k) {
+            const float gd = wall ? dep[k + 1] : dhi;
+            dep[k + 2] = k == kl ? gd : dep[k + 2];
+        }
+    }
+    __syncthreads();
+    float3 f;
+    float4 l;
+    fs_eliminate(tri_k(d.Bd, d.rdx), i0, d.nx, is_wall(d, 0), is_wall(d, 1), glo, ghi, dep, a, b, c, r, f, l);
+    float4 vp[4], ve[4];
+    auto epilogue_loads = [&] {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int q = 4 * (s + m * nseg);
+            vp[m] = live ? *reinterpret_cast<const float4 *>(A.pbase + o + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+            ve[m] = live ? *reinterpret_cast<const float4 *>(A.eraw + o + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    if (EARLY) epilogue_loads();
+    const float2 x = fs_reduced(f, l, s, nseg, 1, lds);
+    fs_back(a, b, c, r, x);
+    __syncthreads();
+    if (row < R)
+#pragma unroll
+        for (int k = 0; k < FM; k += 4)
+            *reinterpret_cast<float4 *>(const_cast<float *>(seg) + k) = make_float4(r[k], r[k + 1], r[k + 2], r[k + 3]);
+    if (!EARLY) epilogue_loads();
+    const float *gx = A.Dc + (size_t)d.ny * d.zpitch;  // sponge factors of the columns
+    const float gy = A.sponge && live ? A.Dc[oz + d.nx] : 1.f;
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+        const int q = 4 * (s + m * nseg);
+        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + oz + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    __syncthreads();
+    int bad = 0;
+    if (live)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            const int qs = s + m * nseg, i = 4 * qs;
+            const float4 dx = *reinterpret_cast<const float4 *>(mine + (qs >> 2) * FMP + 4 * (qs & 3));
+            float4 P = make_float4(vp[m].x + dx.x, vp[m].y + dx.y, vp[m].z + dx.z, vp[m].w + dx.w), e = ve[m];
+            const float4 D = vd[m];
+            const bool i1 = i + 1 < d.nx, i2 = i + 2 < d.nx, i3 = i + 3 < d.nx;
+            P.x = shore(P.x, e.x, D.x, d.eps);
+            P.y = shore(P.y, e.y, D.y, d.eps);
+            P.z = shore(P.z, e.z, D.z, d.eps);
+            P.w = shore(P.w, e.w, D.w, d.eps);
+            if (A.sponge) {
+                const float4 g4 = *reinterpret_cast<const float4 *>(gx + i);
+                const float m0 = D.x > 0.f ? g4.x * gy : 1.f, m1 = D.y > 0.f ? g4.y * gy : 1.f;
+                const float m2 = D.z > 0.f ? g4.z * gy : 1.f, m3 = D.w > 0.f ? g4.w * gy : 1.f;
+                P = make_float4(P.x * m0, P.y * m1, P.z * m2, P.w * m3);
+                e = make_float4(e.x * m0, e.y * m1, e.z * m2, e.w * m3);
+            }
+            bad |= i < d.nx && !(isfinite(P.x) && isfinite(e.x));
+            bad |= i1 && !(isfinite(P.y) && isfinite(e.y));
+            bad |= i2 && !(isfinite(P.z) && isfinite(e.z));
+            bad |= i3 && !(isfinite(P.w) && isfinite(e.w));
+            auto store = [&](float *p, float4 v) {
+                if (i3) {
+                    *reinterpret_cast<float4 *>(p + i) = v;
+                } else {
+                    if (i < d.nx) p[i] = v.x;
+                    if (i1) p[i + 1] = v.y;
+                    if (i2) p[i + 2] = v.z;
+                }
+            };
+            store(A.pout + o, P);
+            if (A.sponge) store(A.eta + o, e);
+        }
+    if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(A.health, 1);
+}
+
+template <bool EARLY>
+__device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T, int g) {
+#pragma clang fp contract(off)
+    const Dom &d = A.d;
+    const int nseg = fs_segs(d.ny), C = fs_cols(T, d.ny);
+    const int t = threadIdx.x, s = t / C, i = g * C + (t & (C - 1)), j0 = s * FM;
+    const bool live = s < nseg && i < d.nx;
+    const int ic = live ? i : 0, jc = live ? j0 : 0, kl = d.ny - 1 - jc;  // kl: the column's last cell
+    // one lane offset per field and uniform row offsets (a lane offset per row
+    // cost 34 registers); the fields hold whole segments of rows, the depth
+    // one row past the last and then other data: what lies past the end is
+    // replaced
+    const unsigned pb = 4u * (unsigned)d.pitch, zb = 4u * (unsigned)d.zpitch;
+    const auto br = bres(ldp(A.rx, A.fstride), A.fstride), bd = bres(A.Dc, zb * (unsigned)d.ny);
+    const auto bq = bres(ldp(A.pbase, A.fstride), A.fstride), be = bres(A.eraw, A.fstride);
+    const auto bo = bres(ldp(A.pout, A.fstride), A.fstride);
+    const unsigned vo = (unsigned)jc * pb + 4u * (unsigned)ic, vz = (unsigned)jc * zb + 4u * (unsigned)ic;
+    float dep[FM + 2], r[FM], a[FM], b[FM], c[FM];
+#pragma unroll
+    for (int k = 0; k < FM; ++k) r[k] = bld(br, vo, k * pb);
+    dep[0] = bld(bd, jc > 0 ? vz - zb : vz, 0);
+#pragma unroll
+    for (int k = 0; k < FM + 1; ++k) dep[k + 1] = bld(bd, vz, k * zb);
+    float glo = 0.f, ghi = 0.f, dlo = 0.f, dhi = 0.f;
+    const bool lo_wall = is_wall(d, 2), hi_wall = is_wall(d, 3);
+    if (!lo_wall && live && s == 0) {
+        glo = A.gh1[ghost_index(d, 2, 0, i + 2) + 2] - A.gh0[ghost_index(d, 2, 0, i + 2) + 2];
+        dlo = 0.25f * ((d.D[i] + d.D[i + 1]) + (d.D[i] + d.D[i + 1]));
+    }
+    if (!hi_wall && live && kl < FM) {
+        ghi = A.gh1[ghost_index(d, 3, 0, i + 2) + 2] - A.gh0[ghost_index(d, 3, 0, i + 2) + 2];
+        const float *Dn = d.D + (size_t)d.ny * d.zpitch;
+        dhi = 0.25f * ((Dn[i] + Dn[i + 1]) + (Dn[i] + Dn[i + 1]));
+    }
+    dep[0] = jc > 0 || lo_wall ? dep[0] : dlo;  // walls: the first and last cells' own depths
+#pragma unroll
+    for (int k = 0; k < FM; ++k) {
+        const float gd = hi_wall ? dep[k + 1] : dhi;
+        dep[k + 2] = k < kl ? dep[k + 2] : gd;
+        r[k] = k <= kl ? r[k] : 0.f;
+    }
+#pragma unroll
+    for (int k = 0; k < FM + 2; ++k) dep[k] = fmaxf(dep[k], 0.f);
+    float3 f;
+    float4 l;
+    fs_eliminate(tri_k(d.Bd, d.rdy), jc, d.ny, is_wall(d, 2), is_wall(d, 3), glo, ghi, dep, a, b, c, r, f, l);
+    float vq[FM], ve[FM], vd[FM];
+    auto epilogue_loads = [&] {
+#pragma unroll
+        for (int k = 0; k < FM; ++k) {
+            vq[k] = bld(bq, vo, k * pb);
+            ve[k] = bld(be, vo, k * pb);
+            vd[k] = bld(bd, vz, k * zb);
+        }
+    };
+    if (EARLY) epilogue_loads();
+    const float2 x = fs_reduced(f, l, s, nseg, C, lds);
+    if (!live) return;
+    fs_back(a, b, c, r, x);
+    if (!EARLY) epilogue_loads();
+#pragma unroll
+    for (int k = 0; k < FM; ++k) r[k] = shore(vq[k] + r[k], ve[k], vd[k], d.eps);
+    if (A.sponge) {
+        const float gx = A.Dc[(size_t)d.ny * d.zpitch + i];
+        float gy[FM];
+#pragma unroll
+        for (int k = 0; k < FM; ++k) gy[k] = ldo(A.Dc, (unsigned)min(jc + k, d.ny - 1) * zb + 4u * (unsigned)d.nx);
+#pragma unroll
+        for (int k = 0; k < FM; ++k) r[k] *= vd[k] > 0.f ? gx * gy[k] : 1.f;
+    }
+    // all values before the first store: left to itself the compiler moves
+    // each row's loads and arithmetic under its store's condition, sixteen
+    // round trips to memory in a row
+#pragma unroll
+    for (int k = 0; k < FM; ++k) asm volatile("" : "+v"(r[k]));
+    int bad = 0;
+#pragma unroll
+    for (int k = 0; k < FM; ++k)
+        if (k <= kl) {
+            bad |= !isfinite(r[k]);
+            bst(bo, vo, k * pb, r[k]);
+        }
+    // lanes that left are not in the vote; one lane of those here reports
+    const unsigned long long v = __ballot(bad);
+    if (v && (int)(threadIdx.x & 63) == __ffsll((long long)v) - 1) atomicOr(A.health, 1);
+}
+
+// Row workgroups first, then column workgroups, neighbours of which share
+// 128-byte lines: consecutive ones to one XCD.
+template <bool EARLY>
+__device__ __forceinline__ void solve_body(const SolveArgs &A, float *lds, int b) {
+    const int T = blockDim.x, nr = fs_row_groups(T, A.d.nx, A.d.ny), nc = fs_col_groups(T, A.d.nx, A.d.ny);
+    if (b < nr) {
+        if (b * fs_rows(T, A.d.nx) < A.d.ny) solve_rows<EARLY>(A, lds, T, b);
+    } else {
+        solve_cols<EARLY>(A, lds, T, xcd_order(b - nr, nc));
+    }
+}
+
+// Up to FS_EARLY threads the registers suffice to have the epilogue's loads in
+// flight across the reduction, which a small grid's few waves need: 128 x 64
+// cells 10.5 -> 9.8 us, 1024 x 512 12.8 -> 12.3.  Larger workgroups load
+// late: 93 registers a lane, five waves a SIMD.
+constexpr int FS_EARLY = 512;
+__global__ __launch_bounds__(FS_EARLY) __attribute__((amdgpu_waves_per_eu(2))) void k_solve(SolveArgs A) {
+    extern __shared__ __align__(16) float fs_buf[];
+    solve_body<true>(A, fs_buf, blockIdx.x);
+}
+__global__ __launch_bounds__(1024) void k_solve_big(SolveArgs A) {
+    extern __shared__ __align__(16) float fs_buf[];
+    solve_body<false>(A, fs_buf, blockIdx.x);
+}
+
+}  // namespace ws

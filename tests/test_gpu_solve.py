@@ -1,0 +1,77 @@
+"""The one-kernel solve of a pass at the edges of its segments, workgroups and
+range, against the FP64 oracle: lines of one cell more and less than whole
+16-cell segments, rows and columns of one segment, the longest columns it
+takes (2048 cells) and the first it leaves to the three-kernel path, a wave
+maker and a sponge on each pair of sides.  The bounds are the parity tests'
+for these step counts: 2e-6 of the wave height after one Euler step, 1e-5
+after the first full step (times sqrt(g d) for the discharges)."""
+import math
+
+import numpy as np
+import pytest
+
+import oracle as o
+from paper_1611_05984_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+A0, DEPTH = 0.03, 0.5
+
+
+def _pair(nx, ny, maker, sponge, **params):
+    from paper_1611_05984_amd import wavestep as ws
+    dx = 0.05
+    rng = np.random.default_rng(nx * 7919 + ny)
+    X = np.arange(nx + 1)[None, :] / nx
+    Y = np.arange(ny + 1)[:, None] / ny
+    z = -0.5 + 0.1 * np.sin(7 * X + 5 * Y + rng.uniform(0, 6)) * np.ones((ny + 1, nx + 1))
+    z = np.where((X > 0.6) & (Y > 0.6), z + 0.45, z)      # a bank that dries in places
+    z = z.astype(np.float32).astype(np.float64)
+    dt = wl.courant_dt(0.2, dx, 0.6)
+    g = ws.Domain(nx, ny, dx, dx, dt, z, **params)
+    r = o.Domain(nx, ny, dx, dx, dt, z, **params)
+    for d in (g, r):
+        if maker is not None:
+            d.set_boundary(maker, ws.WAVES, 2, [0.02, 0.01], [1.5, 0.9], [0.3, -0.2], [0.0, 1.0])
+        if sponge is not None:
+            d.set_boundary(sponge, ws.SPONGE, 5)
+        d.apply_edit(ws.EDIT_WATER, 0.4 * nx * dx, 0.4 * ny * dx, A0, 6 * dx)
+    return g, r
+
+
+@pytest.mark.parametrize("nx,ny,maker,sponge", [
+    (16, 16, 0, 1), (17, 15, 1, 2), (15, 17, 2, 0), (33, 2, 3, 0), (2, 31, None, 3), (129, 256, 0, 3),
+    (130, 257, 3, 1), (1025, 48, 1, 3), (61, 512, 2, 1), (70, 1023, 3, 0), (9, 2048, 2, 1), (65, 2049, 0, 2),
+])
+def test_one_kernel_solve_edges(nx, ny, maker, sponge):
+    print("case: solve %dx%d maker %s sponge %s" % (nx, ny, maker, sponge), flush=True)
+    g, r = _pair(nx, ny, maker, sponge)
+    for n, rel in ((1, 2e-6), (2, 1e-5)):
+        g.advance(n)
+        r.advance(n)
+        got, want = g.state_numpy(), r.state()
+        for k, (a, b) in enumerate(zip(got, want)):
+            scale = A0 * (math.sqrt(9.81 * DEPTH) if k else 1.0)
+            assert np.abs(a - b).max() <= rel * scale, (n, k, np.abs(a - b).max())
+    assert g.query()[2] == 0
+
+
+@pytest.mark.parametrize("solver", [1, 2])
+def test_switching_solvers_keeps_the_one_kernel_path_right(solver):
+    """Other strategies use the same scratch: PCR, the other, PCR again from
+    one snapshot gives PCR's bits; likewise after a rejected terrain edit
+    (which uses the cell-depth field) and after a boundary change."""
+    from paper_1611_05984_amd import wavestep as ws
+    g, _ = _pair(90, 50, 0, 3)
+    g.advance(4)
+    snap = g.snapshot()
+    g.advance(5)
+    want = g.state_numpy()
+    g.set_tuning(8, 128, solver)
+    g.restore(snap)
+    g.advance(5)
+    g.set_tuning(8, 128, ws.SOLVE_PCR)
+    g.restore(snap)
+    assert g.apply_edit(ws.EDIT_TERRAIN, 2.0, 1.0, -400.0, 0.05) == ws.ENOTDD
+    g.advance(5)
+    for a, b in zip(want, g.state_numpy()):
+        assert np.array_equal(a, b)
