@@ -78,6 +78,7 @@ struct ws_domain {
     bool vdirty;                   // pass argument tables must be rewritten
     int sy, pnt, solver;           // tuning: stencil rows per strip, PCR threads per system, reduced solver
     int syc;                       // stencil rows per strip in corrector passes (0: sy)
+    bool fs_zero[3];               // history slots whose F*, G* are known to be zero (NLSW steps)
     bool rows_set;                 // the heights above are the caller's (else short_rows() picks)
     size_t fstride;                // bytes between consecutive fields
     StencilArgs *vsa;              // pass argument tables (device), batch use only
@@ -523,6 +524,7 @@ static ws_status domain_setup(ws_domain *d, const ws_grid *g, const float *z_cor
     d->cur = 0;
     d->step = 0;
     d->t = 0.0;
+    for (bool &z : d->fs_zero) z = true;
     return WS_OK;
 }
 
@@ -842,6 +844,7 @@ extern "C" ws_status ws_restore(ws_domain *d, const void *src_dev, size_t bytes,
     refresh_cells(d, st);
     HIPCHK(hipMemsetAsync(d->health, 0, sizeof(int), st));
     d->cur = 0;
+    for (bool &z : d->fs_zero) z = false;
     // history levels taken at another time step are not spaced by this one:
     // the multistep history restarts (two Euler steps), as after a change of dt
     d->step = h.dt == d->g.dt ? h.step : 0;
@@ -1001,9 +1004,15 @@ static void launch_stencil(const ws_domain *d, int sy, hipStream_t st, const Ste
     const dim3 g1(grid.x * grid.y);  // 1-D grid in XCD-aware tile order
     const int gx = (int)grid.x;
 #define L3(KERN) hipLaunchKernelGGL(KERN, g1, dim3(solo ? 64 : 64 * SWG), 0, st, sa, gx)
-    if (sa.kind == 2) SY_SWITCH(k_stencil_c, sy, L3);
-    else if (sa.kind == 1) SY_SWITCH(k_stencil_p, sy, L3);
-    else SY_SWITCH(k_stencil_e, sy, L3);
+    if (d->g.model == WS_NLSW) {
+        if (sa.kind == 2) SY_SWITCH(k_nlsw_c, sy, L3);
+        else if (sa.kind == 1) SY_SWITCH(k_nlsw_p, sy, L3);
+        else SY_SWITCH(k_nlsw_e, sy, L3);
+    } else {
+        if (sa.kind == 2) SY_SWITCH(k_stencil_c, sy, L3);
+        else if (sa.kind == 1) SY_SWITCH(k_stencil_p, sy, L3);
+        else SY_SWITCH(k_stencil_e, sy, L3);
+    }
 #undef L3
 }
 // Equations per thread for systems of up to nred unknowns: a power of two.
@@ -1091,8 +1100,9 @@ static void launch_solve(const ws_domain *d, hipStream_t st, const SolveArgs &so
 // Arguments of pass p of a step.  cur: state buffer of the step's state;
 // sm: step index mod 3 (history slots); euler: one of the two start-up steps.
 // sponge: the last pass applies the sponge (the tolerance mode does it itself).
+// table: for a batch's tables, which serve steps the host does not follow.
 static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int sm, int p, StencilArgs &sa,
-                      SolveArgs &so, bool sponge = true) {
+                      SolveArgs &so, bool sponge = true, bool table = false) {
     const ws_grid &g = d->g;
     const int K = euler ? 0 : g.n_corr;
     const int n0 = (sm + 2) % 3, n1 = (sm + 1) % 3, n2 = sm;
@@ -1110,8 +1120,14 @@ static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int
     sa.h2 = d->hist[n2][0];
     sa.S = d->S[0];
     sa.fstride = (unsigned)d->fstride;
-    {
-        const double rx = 1.0 / g.dx, ry = 1.0 / g.dy;
+    const double rx = 1.0 / g.dx, ry = 1.0 / g.dy;
+    sa.gx = (float)(g.g * rx);
+    sa.gy = (float)(g.g * ry);
+    if (g.model == WS_NLSW) {
+        sa.pbase = d->st[a][1];
+        sa.cells = d->Dnew;
+        sa.health = d->health;
+    } else {
         sa.hx = (float)(0.5 * rx);
         sa.hy = (float)(0.5 * ry);
         sa.sxx = (float)(rx * rx);
@@ -1121,8 +1137,6 @@ static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int
         sa.cyyy = (float)(0.5 * ry * ry * ry);
         sa.cxyy = (float)(0.5 * rx * ry * ry);
         sa.cxxy = (float)(0.5 * rx * rx * ry);
-        sa.gx = (float)(g.g * rx);
-        sa.gy = (float)(g.g * ry);
         sa.Bg = (float)(g.Bcoef * g.g);
     }
     sa.dt = (float)g.dt;
@@ -1151,9 +1165,11 @@ static void pass_args(const ws_domain *d, const Dom &m, bool euler, int cur, int
     so.luy = d->luy;
     so.layout = (d->solver == WS_SOLVE_LU || d->solver == WS_SOLVE_LU2) ? 1 : 0;
     so.sponge = sponge && p == K ? 1 : 0;
-    so.nlsw = g.model == WS_NLSW ? 1 : 0;
-    sa.split = fused(d) ? 1 : 0;
-    if (sa.split) {
+    if (g.model == WS_NLSW) {
+        if (so.sponge && has_sponges(d)) sa.flags |= F_SPONGE;
+        if (table || !(d->fs_zero[n0] && d->fs_zero[n1] && d->fs_zero[n2])) sa.flags |= F_FS;
+    } else if (fused(d)) {
+        sa.flags |= F_SPLIT;
         // the row half writes the damped surface while the column half reads
         // the surface: the last pass of a domain with sponges leaves it in
         // the first corrector base, which nothing reads any more
@@ -1218,20 +1234,19 @@ static void launch_reduced(const ws_domain *d, hipStream_t st, const SolveArgs &
 
 // The solves of a pass, from the increments to the new discharges.
 static void launch_solves(ws_domain *d, const SolveArgs &so, hipStream_t st) {
+    if (d->g.model == WS_NLSW) return;  // identity systems: the stencil wrote the discharges
     if (fused(d)) {
         ProfScope p(d, st, WS_K_SOLVE);
         launch_solve(d, st, so);
         return;
     }
-    if (!so.nlsw) {  // NLSW: identity systems, nothing to solve
-        {
-            ProfScope p(d, st, WS_K_REDUCE);
-            hipLaunchKernelGGL(k_reduce, tiles(d), dim3(NT), 0, st, so);
-        }
-        {
-            ProfScope p(d, st, WS_K_SOLVE);
-            launch_reduced(d, st, so);
-        }
+    {
+        ProfScope p(d, st, WS_K_REDUCE);
+        hipLaunchKernelGGL(k_reduce, tiles(d), dim3(NT), 0, st, so);
+    }
+    {
+        ProfScope p(d, st, WS_K_SOLVE);
+        launch_reduced(d, st, so);
     }
     {
         ProfScope p(d, st, WS_K_EXPAND);
@@ -1280,6 +1295,7 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
             pass_args(d, m, euler, d->cur, (int)(s % 3), p, sa, so, !conv);
             ws_status r = run_pass(d, sa, so, st);
             if (r != WS_OK) return r;
+            if (p == 0) d->fs_zero[(s + 2) % 3] = d->g.model == WS_NLSW;  // the slot this step's predictor wrote
             if (conv && p >= 1) {
                 // change against the previous iterate (the pass's input state)
                 const int a = d->cur, b1 = (a + 1) % 3, c1 = (a + 2) % 3;
@@ -1365,6 +1381,7 @@ struct ws_batch {
     bool stale = false;                  // device states ahead of the domains' host copies
     int maxK = 0, nred = 0, total[6] = {0, 0, 0, 0, 0, 0};
     int fsT = 256;                       // threads of the one-kernel solve's workgroups
+    bool models[2] = {false, false};     // models among the domains
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
     hipStream_t gstream = nullptr;
@@ -1443,10 +1460,10 @@ static ws_status write_vtab(ws_domain *d) {
     const Dom m = make_dom(d);
     for (int key = 0; key < 9; ++key) {
         const int cur = key / 3, sm = key % 3;
-        pass_args(d, m, true, cur, sm, 0, sa[key], so[key]);
+        pass_args(d, m, true, cur, sm, 0, sa[key], so[key], true, true);
         for (int p = 0; p <= d->g.n_corr; ++p) {
             const int v = 9 + key * (d->g.n_corr + 1) + p;
-            pass_args(d, m, false, cur, sm, p, sa[v], so[v]);
+            pass_args(d, m, false, cur, sm, p, sa[v], so[v], true, true);
         }
     }
     HIPCHK(hipMemcpy(d->vsa, sa.data(), sizeof(StencilArgs) * d->nvar, hipMemcpyHostToDevice));
@@ -1490,18 +1507,21 @@ static ws_status batch_upload(ws_batch *b) {
     const int rp0 = b->rp, rc0 = b->rc;
     batch_rows(b, order);
     int fsT = 256;
+    bool models[2] = {false, false};
     for (int k = 0; k < n; ++k) {
         ws_domain *d = b->slots[order[k]];
         if (d->solver != b->solver) {  // the batch's solve strategy (and layout) applies
             d->solver = b->solver;
             d->vdirty = true;
         }
+        for (bool &z : d->fs_zero) z = false;  // the host does not follow the batch's steps
+        models[d->g.model] = true;
         if (fused(d)) fsT = std::max(fsT, fs_threads(d->g.nx, d->g.ny));
-        else nred = std::max(nred, nred_of(d));
+        else if (d->g.model == WS_BSNQ) nred = std::max(nred, nred_of(d));
     }
     for (int k = 0; k < n; ++k) {
         ws_domain *d = b->slots[order[k]];
-        const bool one = fused(d);
+        const bool one = fused(d), three = !one && d->g.model == WS_BSNQ;  // how its passes are solved
         if (d->vdirty) {
             ws_status r = write_vtab(d);
             if (r != WS_OK) return r;
@@ -1515,11 +1535,11 @@ static ws_status batch_upload(ws_batch *b) {
         b->h_state[k].health = 0;
         const BatchDesc &D = desc[k];
         pre[0][k + 1] = pre[0][k] + D.sgx * D.sgy;
-        pre[1][k + 1] = pre[1][k] + (one ? 0 : D.tgx * D.tgy);
+        pre[1][k + 1] = pre[1][k] + (three ? D.tgx * D.tgy : 0);
         pre[5][k + 1] = pre[5][k] + (one ? fs_row_groups(fsT, D.d.nx, D.d.ny) + fs_col_groups(fsT, D.d.nx, D.d.ny) : 0);
         const dim3 sgc = strips_for(d, b->rc, true);  // the corrector's one-wave grid
         pre[4][k + 1] = pre[4][k] + (int)(sgc.x * sgc.y);
-        pre[2][k + 1] = pre[2][k] + (one                                           ? 0
+        pre[2][k + 1] = pre[2][k] + (!three                                        ? 0
                                      : b->solver == WS_SOLVE_LU2                   ? solve2_waves(D.d.nx, D.d.ny)
                                      : b->solver == WS_SOLVE_LU && luw_waves(nred) ? luw_groups(D.d.nx, D.d.ny)
                                      : b->solver != WS_SOLVE_PCR && b->solver != WS_SOLVE_PCR_WAVE
@@ -1535,13 +1555,14 @@ static ws_status batch_upload(ws_batch *b) {
             HIPCHK(hipMemcpy(b->d_pre[q], pre[q].data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice));
     }
     bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0 &&
-                fsT == b->fsT;
+                fsT == b->fsT && models[0] == b->models[0] && models[1] == b->models[1];
     for (int q = 0; q < 6; ++q) same = same && pre[q][n] == b->total[q];
     if (!same) batch_drop_graph(b);
     b->order = order;
     b->maxK = maxK;
     b->nred = nred;
     b->fsT = fsT;
+    for (int q = 0; q < 2; ++q) b->models[q] = models[q];
     for (int q = 0; q < 6; ++q) b->total[q] = pre[q][n];
     b->dirty = false;
     return WS_OK;
@@ -1559,7 +1580,7 @@ static void batch_solves(ws_batch *b, hipStream_t st, int p) {
             hipLaunchKernelGGL(kb_solve_big, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5],
                                n, p);
     }
-    if (b->total[1] == 0) return;
+    if (b->total[1] == 0) return;  // no domain on the three-kernel path
     hipLaunchKernelGGL(kb_reduce, dim3(b->total[1]), dim3(NTB), 0, st, b->d_desc, b->d_state, b->d_pre[1], n, p);
     const dim3 pg(b->total[2]);
     const size_t shm = sizeof(float4) * b->nred;
@@ -1595,10 +1616,19 @@ static ws_status batch_step(ws_batch *b, hipStream_t st) {
         const int q = p > 0 ? 4 : 0, rows = p > 0 ? b->rc : b->rp;
         const dim3 sg(b->total[q]);
 #define L4(KERN) hipLaunchKernelGGL(KERN, sg, dim3(p > 0 ? 64 : 64 * SWG), 0, st, b->d_desc, b->d_state, b->d_pre[q], n, p)
-        if (p > 0) SY_SWITCH(kb_stencil_c, rows, L4);
-        else {
-            SY_SWITCH(kb_stencil_e, rows, L4);
-            SY_SWITCH(kb_stencil_p, rows, L4);
+        if (b->models[WS_BSNQ]) {
+            if (p > 0) SY_SWITCH(kb_stencil_c, rows, L4);
+            else {
+                SY_SWITCH(kb_stencil_e, rows, L4);
+                SY_SWITCH(kb_stencil_p, rows, L4);
+            }
+        }
+        if (b->models[WS_NLSW]) {
+            if (p > 0) SY_SWITCH(kb_nlsw_c, rows, L4);
+            else {
+                SY_SWITCH(kb_nlsw_e, rows, L4);
+                SY_SWITCH(kb_nlsw_p, rows, L4);
+            }
         }
 #undef L4
         batch_solves(b, st, p);
@@ -1866,6 +1896,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     StencilArgs sp;
     SolveArgs sop;
     pass_args(d, m, d->step + 1 <= 2, d->cur, (int)((d->step + 1) % 3), 0, sp, sop);
+    if (d->g.model == WS_NLSW) sa.health = sp.health = (int *)d->scal;  // (its stencil reports the health)
     const int rows[6] = {8, 16, 24, 32, 48, 64};
     float t_rows[2][6];
     for (int c = 0; c < 6; ++c) t_rows[0][c] = t_rows[1][c] = 1e30f;
@@ -1934,15 +1965,16 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     const bool prof = d->prof_on;
     d->prof_on = false;
     d->solver = WS_SOLVE_PCR;
-    if (fused(d)) {
+    if (d->g.model == WS_NLSW) {
+        // nothing to solve: the defaults stay
+    } else if (fused(d)) {
         time_solves(WS_SOLVE_PCR, PCR_NT);  // the thread counts and the wave form are the same kernel
     } else {
         for (int c : {64, 128, 256}) time_solves(WS_SOLVE_PCR, c);
         if (pcrw_fits(nred_of(d))) time_solves(WS_SOLVE_PCR_WAVE, keep_pnt);  // (same bits as the above)
     }
-    time_solves(WS_SOLVE_THOMAS, keep_pnt);
-    time_solves(WS_SOLVE_LU, keep_pnt);
-    time_solves(WS_SOLVE_LU2, keep_pnt);
+    if (d->g.model != WS_NLSW)
+        for (int sv : {WS_SOLVE_THOMAS, WS_SOLVE_LU, WS_SOLVE_LU2}) time_solves(sv, keep_pnt);
     d->solver = keep;
     d->pnt = keep_pnt;
     d->prof_on = prof;
@@ -2005,8 +2037,14 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
             ms[p] = time_it([&] {
                 const dim3 sg(b->total[p > 0 ? 4 : 0]);
 #define L5(KERN) hipLaunchKernelGGL(KERN, sg, dim3(p > 0 ? 64 : 64 * SWG), 0, st, b->d_desc, b->d_state, b->d_pre[p > 0 ? 4 : 0], n, p)
-                if (p > 0) SY_SWITCH(kb_stencil_c, b->sy, L5);
-                else SY_SWITCH(kb_stencil_p, b->sy, L5);
+                if (b->models[WS_BSNQ]) {
+                    if (p > 0) SY_SWITCH(kb_stencil_c, b->sy, L5);
+                    else SY_SWITCH(kb_stencil_p, b->sy, L5);
+                }
+                if (b->models[WS_NLSW]) {
+                    if (p > 0) SY_SWITCH(kb_nlsw_c, b->sy, L5);
+                    else SY_SWITCH(kb_nlsw_p, b->sy, L5);
+                }
 #undef L5
             });
         tp[c] = ms[0];
@@ -2031,7 +2069,7 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     if ((r = batch_upload(b)) != WS_OK) return r;
     const int n = (int)b->order.size();
     best = 1e30f;
-    if (n > 0) {
+    if (n > 0 && b->models[WS_BSNQ]) {
         // each strategy timed as all the solves of a corrector pass
         auto time_solves = [&](int solver, int pnt) -> ws_status {
             b->solver = solver;

@@ -85,22 +85,25 @@ __device__ __forceinline__ int find_dom(const int *prefix, int ndom, int b) {
 // that of domains taking full steps (each domain's predictor runs in exactly
 // one of the two launches), 2 for the corrector passes.  The bodies are the
 // single-domain kernels' own, so both give the same bits.
-template <int SYT, int KIND>
+// NL: the launch for the domains in the NLSW model (whole passes), the other for
+// those in the dispersive one.
+template <int SYT, int KIND, bool NL = false>
 __device__ __forceinline__ void kb_stencil_body(const BatchDesc *__restrict__ descs, const BatchState *__restrict__ states,
                                                 const int *__restrict__ prefix, int ndom, int p) {
     // XCD-aware order over all strips of all domains (as in k_stencil_*)
     const int b = xcd_order(blockIdx.x, gridDim.x), dm = find_dom(prefix, ndom, b);
     const BatchDesc &D = descs[dm];
     const BatchState &S = states[dm];
+    if ((D.d.model == NLSW) != NL) return;                      // the other model's launch
     if (KIND < 2 && (S.step + 1 <= 2) != (KIND == 0)) return;  // the other predictor launch's domain
     const int v = variant(D, S, p);
     if (v < 0) return;
     const int local = b - prefix[dm];
     const StencilArgs A = load_params(D.sa + v);
     if constexpr (KIND == 2)  // one-wave workgroups, as the single-domain corrector
-        stencil_body<SYT, 2, true>(A, local % D.sgxc, local / D.sgxc);
+        stencil_body<SYT, 2, true, NL>(A, local % D.sgxc, local / D.sgxc);
     else
-        stencil_body<SYT, KIND>(A, local % D.sgx, local / D.sgx);
+        stencil_body<SYT, KIND, false, NL>(A, local % D.sgx, local / D.sgx);
 }
 template <int SYT>
 __global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void kb_stencil_e(const BatchDesc *__restrict__ descs,
@@ -119,6 +122,25 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void kb
                                                          const BatchState *__restrict__ states,
                                                          const int *__restrict__ prefix, int ndom, int p) {
     kb_stencil_body<SYT, 2>(descs, states, prefix, ndom, p);
+}
+
+template <int SYT>
+__global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void kb_nlsw_e(const BatchDesc *__restrict__ descs,
+                                                         const BatchState *__restrict__ states,
+                                                         const int *__restrict__ prefix, int ndom, int p) {
+    kb_stencil_body<SYT, 0, true>(descs, states, prefix, ndom, p);
+}
+template <int SYT>
+__global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void kb_nlsw_p(const BatchDesc *__restrict__ descs,
+                                                         const BatchState *__restrict__ states,
+                                                         const int *__restrict__ prefix, int ndom, int p) {
+    kb_stencil_body<SYT, 1, true>(descs, states, prefix, ndom, p);
+}
+template <int SYT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void kb_nlsw_c(const BatchDesc *__restrict__ descs,
+                                                         const BatchState *__restrict__ states,
+                                                         const int *__restrict__ prefix, int ndom, int p) {
+    kb_stencil_body<SYT, 2, true>(descs, states, prefix, ndom, p);
 }
 
 // The batch's tile kernels run two-wave workgroups (NTB threads): over many

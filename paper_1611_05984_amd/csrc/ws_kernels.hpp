@@ -38,6 +38,10 @@ namespace ws {
 // Field groups are consecutive fields of the workspace, fstride bytes apart:
 // a group is addressed by one base pointer plus k * fstride, which keeps the
 // kernel's uniform registers few (every field pointer would not fit in SGPRs).
+// F_SPLIT: the increments as two fields (one-kernel solve) instead of packed
+// pairs.  NLSW: F_SPONGE applies the sponge; F_FS: the history slots the step
+// touches may hold F*, G* of the dispersive model (else they are all zero).
+enum { F_SPLIT = 1, F_SPONGE = 2, F_FS = 4 };
 struct StencilArgs {
     Dom d;
     const float *in;     // estimate read (the state itself for the predictor): eta, P, Q
@@ -48,14 +52,20 @@ struct StencilArgs {
     const float *h2;     // level n-2
     float *S;            // corrector bases: eta, U* and V* increments
     unsigned fstride;    // bytes between consecutive fields of a group
-    // grid-spacing factors of the difference formulas, premultiplied:
-    // hx = 1/(2dx), sxx = 1/dx^2, cxy = 1/(4 dx dy), cxxx = 1/(2 dx^3),
-    // cxyy = 1/(2 dx dy^2), gx = g/dx, Bg = B g (y analogues likewise)
-    float hx, hy, sxx, syy, cxy, cxxx, cyyy, cxyy, cxxy, gx, gy, Bg;
+    int flags;           // F_*
+    union {
+        // dispersive model: grid-spacing factors of the difference formulas,
+        // premultiplied: hx = 1/(2dx), sxx = 1/dx^2, cxy = 1/(4 dx dy), cxxx =
+        // 1/(2 dx^3), cxyy = 1/(2 dx dy^2), Bg = B g (y analogues likewise)
+        struct { float hx, hy, sxx, syy, cxy, cxxx, cyyy, cxyy, cxxy, Bg; };
+        // NLSW: P^n of the step (Q^n one field on), the cell field (sponge
+        // factors), the health word
+        struct { const float *pbase, *cells; int *health; };
+    };
+    float gx, gy;        // g/dx, g/dy
     float dt, x0, x1, x2;  // step, F* extrapolation weights
     int kind;            // 0 Euler predictor, 1 AB3 predictor, 2 AM4 corrector
     int write_S;
-    int split;           // the increments as two fields (one-kernel solve) instead of packed pairs
 };
 
 __device__ __forceinline__ float dcell4(float a, float b, float c, float d) {
@@ -136,6 +146,13 @@ __device__ __forceinline__ void st2(float *p, unsigned ob, float2 v) {
     *reinterpret_cast<float2 *>(reinterpret_cast<char *>(p) + ob) = v;
 }
 
+// Shoreline fix of one discharge: h times the desingularized velocity.
+__device__ __forceinline__ float shore(float m, float e, float Dc, float eps) {
+#pragma clang fp contract(off)
+    const float h = e + Dc, h2 = h * h;
+    return h2 * h2 < eps ? m * (1.41421356237f * h2 * frsq(fmaf(h2, h2, eps))) : m;
+}
+
 // Rows per stencil strip: a template parameter (8, 16, 24, 32, 48 or 64, and
 // 1, 2 or 4 on grids too small to fill the chip otherwise) chosen per grid
 // shape; taller strips spend less on the 4 warm-up rows, shorter ones give
@@ -145,7 +162,12 @@ __device__ __forceinline__ void st2(float *p, unsigned ob, float2 v) {
 // is one wave (one strip) instead of SWG side-by-side strips; the
 // single-domain corrector is 4 % faster so, the predictors 7 % slower.
 // Every cell's arithmetic is the same either way.
-template <int SYT, int KIND, bool SOLO = false>
+// NL: the NLSW model.  Its systems of eqs. 21-22 are the identity, so the
+// increments are final: the kernel writes P and Q itself (P^n + dP, shoreline
+// fix, sponge) and a pass is this one launch; before, the increments went to
+// memory and an expansion launch read them, P^n, Q^n, the surface and the depth
+// back (2048 x 1500 cells, two correctors: 1.49 -> 1.07 ms for 8 steps).
+template <int SYT, int KIND, bool SOLO = false, bool NL = false>
 __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int by) {
     const Dom &d = A.d;
     constexpr int kind = KIND;
@@ -182,6 +204,8 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
 
     const unsigned F1 = A.fstride, F2 = 2u * A.fstride, F3b = 3u * A.fstride;
     const float *pin = ldp(A.in, F1), *qin = ldp(A.in, F2);
+    int bad = 0;
+    const float gcol = NL && (A.flags & F_SPONGE) && col < d.nx && col >= 0 ? A.cells[(size_t)d.ny * d.zpitch + col] : 1.f;
     // row r + 1 is loaded while row r is computed
     float ne = 0.f, np = 0.f, nq = 0.f, nhe = 0.f, nhp = 0.f, nhq = 0.f, nDl = 0.f, nDr = 0.f;
     auto load_row = [&](int r) {
@@ -247,20 +271,23 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
             const bool out = lane >= 1 && lane <= 62 && col < d.nx && u < d.ny;
             const unsigned o = (unsigned)(u * d.pitch + col) * 4u;  // byte offset (used by output lanes only)
             float E1v = 0.f, F1v = 0.f, G1v = 0.f, Fs1v = 0.f, Gs1v = 0.f, E2v = 0.f, F2v = 0.f, G2v = 0.f;
-            float Fs2v = 0.f, Gs2v = 0.f, Sev = 0.f, SUv = 0.f, SVv = 0.f;
+            float Fs2v = 0.f, Gs2v = 0.f, Sev = 0.f, SUv = 0.f, SVv = 0.f, Pnv = 0.f, Qnv = 0.f;
             if (out) {
                 if (kind == 1) {
                     const f3 l1 = ld3(A.h1, 3u * o), l2 = ld3(A.h2, 3u * o);
-                    const float2 s1 = ld2(A.h1, F3b + 2u * o);
                     E1v = l1.x; F1v = l1.y; G1v = l1.z;
-                    Fs1v = s1.x; Gs1v = s1.y;
                     E2v = l2.x; F2v = l2.y; G2v = l2.z;
-                    if (A.x2 != 0.f) {
-                        const float2 s2 = ld2(A.h2, F3b + 2u * o);
-                        Fs2v = s2.x; Gs2v = s2.y;
+                    if (!NL || (A.flags & F_FS)) {
+                        const float2 s1 = ld2(A.h1, F3b + 2u * o);
+                        Fs1v = s1.x; Gs1v = s1.y;
+                        if (A.x2 != 0.f) {
+                            const float2 s2 = ld2(A.h2, F3b + 2u * o);
+                            Fs2v = s2.x; Gs2v = s2.y;
+                        }
                     }
                 } else if (kind == 2) {
                     Sev = ldo(A.S, o); SUv = ldo(A.S, o + F1); SVv = ldo(A.S, o + F2);
+                    if (NL) { Pnv = ldo(A.pbase, o); Qnv = ldo(A.pbase, o + F1); }
                 }
             }
             // cell and face still-water depths
@@ -287,9 +314,8 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
             const float dep = fmaxf(Dc, 0.f);
             const float dxm = shr1z(dep), dxp = shl1z(dep);
             const float dym = fmaxf(Dcm, 0.f), dyp = fmaxf(Dcp, 0.f);
-            const float ddx = (dxp - dxm) * A.hx, ddy = (dyp - dym) * A.hy;
-
-            if (d.model == BSNQ) {
+            if (!NL) {
+                const float ddx = (dxp - dxm) * A.hx, ddy = (dyp - dym) * A.hy;
                 const float em2 = shr1z(em), ep2 = shl1z(ep);
                 const float epp = shl1z(e3), epm = shl1z(e1);
                 const float emp = shr1z(e3), emm = shr1z(e1);
@@ -349,10 +375,26 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
                 }
                 if (kind != 2) {
                     st3(A.h0, 3u * o, f3{E, F, G});
-                    st2(A.h0, F3b + 2u * o, make_float2(Fs, Gs));
+                    if (!NL || (A.flags & F_FS)) st2(A.h0, F3b + 2u * o, make_float2(Fs, Gs));
                 }
-                sto(A.eout, o, fmaxf(en, -Dc));
-                if (A.split) {
+                en = fmaxf(en, -Dc);
+                if (NL) {
+                    // predictors start from the step's own state
+                    U = shore((kind == 2 ? Pnv : p1) + U, en, Dc, eps);
+                    V = shore((kind == 2 ? Qnv : q1) + V, en, Dc, eps);
+                    if ((A.flags & F_SPONGE) && Dc > 0.f) {
+                        const float gm = gcol * A.cells[(size_t)u * d.zpitch + d.nx];
+                        en *= gm;
+                        U *= gm;
+                        V *= gm;
+                    }
+                    bad |= !(isfinite(U) && isfinite(V) && isfinite(en));
+                    sto(A.eout, o + F1, U);
+                    sto(A.eout, o + F2, V);
+                }
+                sto(A.eout, o, en);
+                if (NL) {
+                } else if (A.flags & F_SPLIT) {
                     sto(A.rxy, o, U);
                     sto(A.rxy, o + F1, V);
                 } else {
@@ -367,6 +409,7 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
         Dcm = Dc0;
         Dc0 = Dcp;
     }
+    if (NL && __ballot(bad) && lane == 0) atomicOr(A.health, 1);
 }
 
 // XCD-aware order of a 1-D grid of G workgroups over a gx x gy tile grid.
@@ -386,11 +429,11 @@ __device__ __forceinline__ void xcd_tile(int b, int G, int gx, int &bx, int &by)
 
 // One kernel per pass kind: Euler start-up predictor, AB3 predictor, AM4
 // corrector.
-template <int SYT, int KIND>
+template <int SYT, int KIND, bool NL = false>
 __device__ __forceinline__ void stencil_kernel_body(const StencilArgs &A, int gx) {
     int bx, by;
     xcd_tile(blockIdx.x, gridDim.x, gx, bx, by);
-    stencil_body<SYT, KIND, KIND == 2>(A, bx, by);  // the corrector on one-wave workgroups
+    stencil_body<SYT, KIND, KIND == 2, NL>(A, bx, by);  // the corrector on one-wave workgroups
 }
 template <int SYT>
 __global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void k_stencil_e(StencilArgs A, int gx) {
@@ -403,6 +446,20 @@ __global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) v
 template <int SYT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_stencil_c(StencilArgs A, int gx) {
     stencil_kernel_body<SYT, 2>(A, gx);
+}
+
+// The same in the NLSW model, each a whole pass.
+template <int SYT>
+__global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void k_nlsw_e(StencilArgs A, int gx) {
+    stencil_kernel_body<SYT, 0, true>(A, gx);
+}
+template <int SYT>
+__global__ __launch_bounds__(64 * SWG) __attribute__((amdgpu_waves_per_eu(4))) void k_nlsw_p(StencilArgs A, int gx) {
+    stencil_kernel_body<SYT, 1, true>(A, gx);
+}
+template <int SYT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_nlsw_c(StencilArgs A, int gx) {
+    stencil_kernel_body<SYT, 2, true>(A, gx);
 }
 
 // ------------------------------------------------------------- solver parts
@@ -427,7 +484,6 @@ struct SolveArgs {
     int *health;
     int sponge;
     unsigned fstride;  // bytes between consecutive fields
-    int nlsw;  // NLSW: the systems are the identity, the increments in rx, ry are final
 };
 
 constexpr int TXP = TX + 1;  // padded LDS row: segment k of row r starts at bank r + 16k
@@ -501,12 +557,12 @@ __device__ __forceinline__ void seg_coefs(const SolveArgs &A, const SolveTile &s
                                           int x0, int y0, float (&a)[M], float (&b)[M], float (&c)[M],
                                           float *r, int st) {
     const Dom &d = A.d;
-    // INNER: a segment clear of the domain's edges (in the dispersive model)
+    // INNER: a segment clear of the domain's edges
     // takes a path without boundary rows, cells outside or per-cell tests;
     // the same arithmetic as the general loop below (used where the
     // duplicated code pays: the reduction, not the expansion)
     const int fi = i0 + x0, fj = j0 + y0;
-    const bool inner = INNER && d.model != NLSW &&
+    const bool inner = INNER &&
                        (dir == 0 ? fj < d.ny && fi >= 1 && fi + M <= d.nx - 1 : fi < d.nx && fj >= 1 && fj + M <= d.ny - 1);
     const TriK tk = tri_k(d.Bd, dir == 0 ? d.rdx : d.rdy);
     if (inner) {
@@ -1267,10 +1323,7 @@ __device__ __forceinline__ void expand_body(const SolveArgs &A, SolveTile &s, in
         pre_q[m] = in ? ldp(A.pbase, A.fstride)[o] : 0.f;
     }
     stage_tile<T>(A, s, i0, j0);
-    if (A.nlsw) {
-        // identity systems (eq. 21-22 with the dispersive coefficients zero):
-        // the partitioned solve would return the increments unchanged
-    } else if (tid < 64) {
+    if (tid < 64) {
         const int row = tid % 16, seg = tid / 16, k0 = seg * MX;
         const int k = 2 * (bx * (TX / MX) + seg), j = j0 + row;
         float x0 = 0.f, xl = 0.f;

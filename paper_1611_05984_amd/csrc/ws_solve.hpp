@@ -172,12 +172,6 @@ __device__ __forceinline__ void fs_back(const float (&a)[FM], const float (&b)[F
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// Shoreline fix of one discharge: h times the desingularized velocity.
-__device__ __forceinline__ float shore(float m, float e, float Dc, float eps) {
-    const float h = e + Dc, h2 = h * h;
-    return h2 * h2 < eps ? m * (1.41421356237f * h2 * frsq(fmaf(h2, h2, eps))) : m;
-}
-
 // Depth of the ghost cell behind a wave-maker side: the side's corners held.
 __device__ __forceinline__ float held_depth(const float *D, size_t c0, size_t c1) {
     return fmaxf(0.25f * ((D[c0] + D[c0]) + (D[c1] + D[c1])), 0.f);

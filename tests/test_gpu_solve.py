@@ -75,3 +75,31 @@ def test_switching_solvers_keeps_the_one_kernel_path_right(solver):
     g.advance(5)
     for a, b in zip(want, g.state_numpy()):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("nx,ny,sponge", [(62, 9, 1), (63, 40, 2), (130, 77, 3)])
+def test_nlsw_passes_follow_model_changes(nx, ny, sponge):
+    """NLSW passes write the discharges from the stencil and, alone, leave out
+    the F*, G* history they know to be zero; a batch never leaves it out.  One
+    start-up, then NLSW, the dispersive model and NLSW again: the same bits
+    alone and in a batch, and the oracle's state within the parity bound."""
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: nlsw %dx%d sponge %s" % (nx, ny, sponge), flush=True)
+    a, r = _pair(nx, ny, 0, sponge, model=1)
+    b, _ = _pair(nx, ny, 0, sponge, model=1)
+    B = ws.Batch(1)
+    slot = B.attach(b)
+    for model, n in ((1, 5), (0, 4), (1, 2), (0, 3), (1, 6)):
+        a.update(model=model)
+        b.update(model=model)
+        a.advance(n)
+        B.advance(n)
+        B.sync()
+        for x, y in zip(a.state_numpy(), b.state_numpy()):
+            assert np.isfinite(x).all() and np.array_equal(x, y), (model, n)
+        if (model, n) == (1, 5):
+            r.advance(5)
+            for k, (x, y) in enumerate(zip(a.state_numpy(), r.state())):
+                assert np.abs(x - y).max() <= 1e-5 * A0 * (math.sqrt(9.81 * DEPTH) if k else 1.0), k
+    B.detach(slot)
+    B.close()
