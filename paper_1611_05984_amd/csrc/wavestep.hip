@@ -1092,7 +1092,11 @@ static bool fused(const ws_domain *d) {
 static void launch_solve(const ws_domain *d, hipStream_t st, const SolveArgs &so) {
     const int T = fs_threads(d->g.nx, d->g.ny);
     const dim3 grid(fs_row_groups(T, d->g.nx, d->g.ny) + fs_col_groups(T, d->g.nx, d->g.ny));
-    if (T <= FS_EARLY) hipLaunchKernelGGL(k_solve, grid, dim3(T), fs_lds(T), st, so);
+    if (d->g.ny > FS_TALL) {
+        const int need = fs_segs(d->g.nx), Tr = need <= 256 ? 256 : (need + 63) / 64 * 64, R = fs_rows(Tr, d->g.nx);
+        hipLaunchKernelGGL(k_solve_rows, dim3((d->g.ny + R - 1) / R), dim3(Tr), fs_lds(Tr), st, so);
+        hipLaunchKernelGGL(k_solve_cols, dim3(fs_col_groups(T, d->g.nx, d->g.ny)), dim3(T), fs_lds(T), st, so);
+    } else if (T <= FS_EARLY) hipLaunchKernelGGL(k_solve, grid, dim3(T), fs_lds(T), st, so);
     else hipLaunchKernelGGL(k_solve_big, grid, dim3(T), fs_lds(T), st, so);
 }
 
@@ -1381,6 +1385,7 @@ struct ws_batch {
     bool stale = false;                  // device states ahead of the domains' host copies
     int maxK = 0, nred = 0, total[6] = {0, 0, 0, 0, 0, 0};
     int fsT = 256;                       // threads of the one-kernel solve's workgroups
+    bool tall = false;                   // some domain on that path has tall columns
     bool models[2] = {false, false};     // models among the domains
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1507,7 +1512,7 @@ static ws_status batch_upload(ws_batch *b) {
     const int rp0 = b->rp, rc0 = b->rc;
     batch_rows(b, order);
     int fsT = 256;
-    bool models[2] = {false, false};
+    bool tall = false, models[2] = {false, false};
     for (int k = 0; k < n; ++k) {
         ws_domain *d = b->slots[order[k]];
         if (d->solver != b->solver) {  // the batch's solve strategy (and layout) applies
@@ -1516,7 +1521,10 @@ static ws_status batch_upload(ws_batch *b) {
         }
         for (bool &z : d->fs_zero) z = false;  // the host does not follow the batch's steps
         models[d->g.model] = true;
-        if (fused(d)) fsT = std::max(fsT, fs_threads(d->g.nx, d->g.ny));
+        if (fused(d)) {
+            fsT = std::max(fsT, fs_threads(d->g.nx, d->g.ny));
+            tall = tall || d->g.ny > FS_TALL;
+        }
         else if (d->g.model == WS_BSNQ) nred = std::max(nred, nred_of(d));
     }
     for (int k = 0; k < n; ++k) {
@@ -1555,13 +1563,14 @@ static ws_status batch_upload(ws_batch *b) {
             HIPCHK(hipMemcpy(b->d_pre[q], pre[q].data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice));
     }
     bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0 &&
-                fsT == b->fsT && models[0] == b->models[0] && models[1] == b->models[1];
+                fsT == b->fsT && tall == b->tall && models[0] == b->models[0] && models[1] == b->models[1];
     for (int q = 0; q < 6; ++q) same = same && pre[q][n] == b->total[q];
     if (!same) batch_drop_graph(b);
     b->order = order;
     b->maxK = maxK;
     b->nred = nred;
     b->fsT = fsT;
+    b->tall = tall;
     for (int q = 0; q < 2; ++q) b->models[q] = models[q];
     for (int q = 0; q < 6; ++q) b->total[q] = pre[q][n];
     b->dirty = false;
@@ -1574,7 +1583,10 @@ static void batch_solves(ws_batch *b, hipStream_t st, int p) {
     const int n = (int)b->order.size();
     if (b->total[5] > 0) {
         const int T = b->fsT;
-        if (T <= FS_EARLY)
+        if (b->tall)
+            hipLaunchKernelGGL(kb_solve_tall, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5],
+                               n, p);
+        else if (T <= FS_EARLY)
             hipLaunchKernelGGL(kb_solve, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5], n, p);
         else
             hipLaunchKernelGGL(kb_solve_big, dim3(b->total[5]), dim3(T), fs_lds(T), st, b->d_desc, b->d_state, b->d_pre[5],

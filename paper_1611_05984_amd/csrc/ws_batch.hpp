@@ -218,7 +218,7 @@ __global__ __launch_bounds__(NTB) void kb_expand(const BatchDesc *__restrict__ d
 // The one-kernel solve over a batch, with the workgroup size the largest of
 // its domains needs.  Domains on the three-kernel path have no workgroups
 // here, and the others none in those kernels.
-template <bool EARLY>
+template <bool EARLY, bool TALL = false>
 __device__ __forceinline__ void kb_solve_body(const BatchDesc *descs, const BatchState *states, const int *prefix,
                                               int ndom, int p, float *lds) {
     const int b = blockIdx.x, dm = find_dom(prefix, ndom, b);
@@ -226,7 +226,7 @@ __device__ __forceinline__ void kb_solve_body(const BatchDesc *descs, const Batc
     const int v = variant(D, states[dm], p);
     if (v < 0) return;
     const SolveArgs A = load_params(D.so + v);
-    solve_body<EARLY>(A, lds, b - prefix[dm]);
+    solve_body<EARLY, TALL>(A, lds, b - prefix[dm]);
 }
 __global__ __launch_bounds__(FS_EARLY) __attribute__((amdgpu_waves_per_eu(2))) void kb_solve(
     const BatchDesc *__restrict__ descs, const BatchState *__restrict__ states, const int *__restrict__ prefix,
@@ -239,6 +239,14 @@ __global__ __launch_bounds__(1024) void kb_solve_big(const BatchDesc *__restrict
                                                      const int *__restrict__ prefix, int ndom, int p) {
     extern __shared__ __align__(16) float fs_buf[];
     kb_solve_body<false>(descs, states, prefix, ndom, p, fs_buf);
+}
+
+// The same where some domain's columns are tall.
+__global__ __launch_bounds__(1024) void kb_solve_tall(const BatchDesc *__restrict__ descs,
+                                                      const BatchState *__restrict__ states,
+                                                      const int *__restrict__ prefix, int ndom, int p) {
+    extern __shared__ __align__(16) float fs_buf[];
+    kb_solve_body<false, true>(descs, states, prefix, ndom, p, fs_buf);
 }
 
 // Reduced systems by lane-per-system Thomas: workgroup (one wave) b - prefix

@@ -28,25 +28,27 @@
 namespace ws {
 
 constexpr int FM = 16;    // cells a lane owns
-constexpr int FMP = 20;   // their LDS stride (floats)
-constexpr int FS_MAXSEG = 128;  // column segments a workgroup takes at most (8 columns a run: 2048 rows)
+constexpr int FMT = 32;   // the same in columns of more than FS_TALL cells
+constexpr int FMP = 20;   // LDS stride of a row segment (floats)
+constexpr int FS_TALL = 2048;  // 128 segments x 8 columns: a workgroup's 1024 lanes
+__host__ __device__ constexpr int fs_m(int ny) { return ny > FS_TALL ? FMT : FM; }
 
 // Threads of a workgroup (T, whole waves): 8 columns a run, at least one
 // whole row, at least 256.  Runs of 16 columns (64 bytes) halve the lines a
 // column workgroup shares with its neighbours, but also the workgroups: us a
 // solve at 16 / 8 / 4 columns: 601 x 601 14.2 / 12.6 / 12.8, 1024 x 512 12.3 /
 // 11.7 / 11.9, 1024 x 1024 20.0 / 17.3 / 18, 2048 x 1500 (8) 39.6 / (4) 41.
-__host__ __device__ constexpr int fs_segs(int n) { return (n + FM - 1) / FM; }
+__host__ __device__ constexpr int fs_segs(int n, int M = FM) { return (n + M - 1) / M; }
 inline int fs_threads(int nx, int ny) {
-    const int need = 8 * fs_segs(ny), m = need > fs_segs(nx) ? need : fs_segs(nx);
+    const int need = 8 * fs_segs(ny, fs_m(ny)), m = need > fs_segs(nx) ? need : fs_segs(nx);
     return m <= 256 ? 256 : (m + 63) / 64 * 64;
 }
-inline bool fs_fits(int nx, int ny) { return fs_segs(ny) <= FS_MAXSEG && fs_segs(nx) <= 1024; }
+inline bool fs_fits(int nx, int ny) { return ny <= 2 * FS_TALL && fs_segs(nx) <= 1024; }
 // Rows of a row workgroup, columns of a column workgroup (a power of two, at
 // most 64), workgroups of each (rows padded to the 8 XCDs).
 __host__ __device__ inline int fs_rows(int T, int nx) { return T / fs_segs(nx); }
-__host__ __device__ inline int fs_cols(int T, int ny) {
-    const int c = T / fs_segs(ny);
+__host__ __device__ inline int fs_cols(int T, int ny, int M) {
+    const int c = T / fs_segs(ny, M);
     return c >= 64 ? 64 : c >= 32 ? 32 : c >= 16 ? 16 : 8;
 }
 __host__ __device__ inline int fs_row_groups(int T, int nx, int ny) {
@@ -54,30 +56,32 @@ __host__ __device__ inline int fs_row_groups(int T, int nx, int ny) {
     return ((ny + r - 1) / r + 7) / 8 * 8;
 }
 __host__ __device__ inline int fs_col_groups(int T, int nx, int ny) {
-    const int c = fs_cols(T, ny);
+    const int c = fs_cols(T, ny, fs_m(ny));
     return (nx + c - 1) / c;
 }
 constexpr size_t fs_lds(int T) { return (size_t)T * FMP * sizeof(float); }
 
-// One segment: cells i0 .. i0 + FM - 1 of a line of n cells, dep[k] the
-// still-water depth of cell i0 + k - 1, r the right-hand sides.  Coefficients
-// of eq. 23, and the elimination of the interior: afterwards row k reads
-// a_k x_first + x_k / b_k + c_k x_last = r_k (b holds reciprocals, 1 <= k <=
-// FM - 2); f: x_first = f.z - f.x x_{-1} - f.y x_last; l: l.x x_first +
-// l.y x_last + l.z x_{+1} = l.w.  The line's ends fold as in seg_coefs (glo,
-// ghi: the maker's discharge change, 0 behind a wall), by selects: a branch
-// had the compiler copy all four arrays.  Cells past the end need not be
-// identity rows: no cell of the line refers to them.  Coefficients and
-// forward elimination go cell by cell, with a scheduling fence every few, so
-// that the depths die as the rows are born (64 live values, not 82).
+// One segment of M cells: cells i0 .. i0 + M - 1 of a line of n cells, dep[k]
+// the still-water depth of cell i0 + k - 1, r the right-hand sides.
+// Coefficients of eq. 23, and the elimination of the interior, every row
+// divided by its diagonal (three arrays, not four): afterwards x_k = r_k -
+// a_k x_first - c_k x_last for 1 <= k <= M - 2; f: x_first = f.z - f.x x_{-1} -
+// f.y x_last; l: l.x x_first + l.y x_last + l.z x_{+1} = l.w.  The line's
+// ends fold as in seg_coefs (glo, ghi: the maker's discharge change, 0 behind
+// a wall), by selects: a branch had the compiler copy all the arrays.  Cells
+// past the end need not be identity rows: no cell of the line refers to
+// them.  Coefficients and forward elimination go cell by cell, with a
+// scheduling fence every few, so that the depths die as the rows are born.
+template <int M>
 __device__ __forceinline__ void fs_eliminate(TriK tk, int i0, int n, bool lo_wall, bool hi_wall, float glo, float ghi,
-                                             const float (&dep)[FM + 2], float (&a)[FM], float (&b)[FM],
-                                             float (&c)[FM], float (&r)[FM], float3 &f, float4 &l) {
+                                             const float (&dep)[M + 2], float (&a)[M], float (&c)[M], float (&r)[M],
+                                             float3 &f, float4 &l) {
 #pragma clang fp contract(off)
     const int kl = n - 1 - i0;  // the line's last cell
     const float hw = hi_wall ? 1.f : 0.f;
+    float b0 = 1.f;
 #pragma unroll
-    for (int k = 0; k < FM; ++k) {
+    for (int k = 0; k < M; ++k) {
         const float dc = dep[k + 1], dd = dep[k + 2] - dep[k];
         const float al = tk.kal * (dc * dc), be = tk.kbe * (dc * dd);
         float ak = be - al, bk = fmaf(2.f, al, 1.f), ck = -be - al;
@@ -87,37 +91,33 @@ __device__ __forceinline__ void fs_eliminate(TriK tk, int i0, int n, bool lo_wal
         ck -= cw;
         if (k == 0) {
             const float aw = i0 == 0 ? ak : 0.f;
-            bk = lo_wall ? bk - aw : bk;
+            b0 = lo_wall ? bk - aw : bk;
             r[0] = fmaf(-aw, glo, r[0]);
-            ak -= aw;
-        }
-        if (k == 1) bk = frcp(bk);
-        if (k >= 2 && k <= FM - 2) {
-            const float m = ak * b[k - 1];
-            ak = -m * a[k - 1];
-            bk = frcp(fmaf(-m, c[k - 1], bk));
-            r[k] = fmaf(-m, r[k - 1], r[k]);
-        }
-        if (k == FM - 1) {
-            const float m = ak * b[k - 1];
-            l = make_float4(-m * a[k - 1], fmaf(-m, c[k - 1], bk), ck, fmaf(-m, r[k - 1], r[k]));
+            a[0] = ak - aw;
+            c[0] = ck;
+        } else if (k == M - 1) {
+            l = make_float4(-ak * a[k - 1], fmaf(-ak, c[k - 1], bk), ck, fmaf(-ak, r[k - 1], r[k]));
+        } else if (k == 1) {
+            const float ib = frcp(bk);
+            a[1] = ak * ib;
+            c[1] = ck * ib;
+            r[1] = r[1] * ib;
         } else {
-            a[k] = ak;
-            b[k] = bk;
-            c[k] = ck;
+            const float ib = frcp(fmaf(-ak, c[k - 1], bk)), m = ak * ib;
+            a[k] = -m * a[k - 1];
+            c[k] = ck * ib;
+            r[k] = fmaf(-m, r[k - 1], r[k] * ib);
         }
         if (k % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int k = FM - 3; k >= 1; --k) {
-        const float m = c[k] * b[k + 1];
-        a[k] = fmaf(-m, a[k + 1], a[k]);
-        c[k] = -m * c[k + 1];
-        r[k] = fmaf(-m, r[k + 1], r[k]);
+    for (int k = M - 3; k >= 1; --k) {
+        a[k] = fmaf(-c[k], a[k + 1], a[k]);
+        r[k] = fmaf(-c[k], r[k + 1], r[k]);
+        c[k] = -c[k] * c[k + 1];
     }
-    const float m = c[0] * b[1];
-    const float inv = frcp(fmaf(-m, a[1], b[0]));
-    f = make_float3(a[0] * inv, -m * c[1] * inv, fmaf(-m, r[1], r[0]) * inv);
+    const float inv = frcp(fmaf(-c[0], a[1], b0));
+    f = make_float3(a[0] * inv, -c[0] * c[1] * inv, fmaf(-c[0], r[1], r[0]) * inv);
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -162,13 +162,13 @@ __device__ __forceinline__ float2 fs_reduced(float3 f, float4 l, int s, int nseg
     return make_float2(fmaf(-f.x, xm, fmaf(-f.y, er, f.z)), er);
 }
 
-__device__ __forceinline__ void fs_back(const float (&a)[FM], const float (&b)[FM], const float (&c)[FM],
-                                        float (&r)[FM], float2 x) {
+template <int M>
+__device__ __forceinline__ void fs_back(const float (&a)[M], const float (&c)[M], float (&r)[M], float2 x) {
 #pragma clang fp contract(off)
 #pragma unroll
-    for (int k = 1; k <= FM - 2; ++k) r[k] = fmaf(-a[k], x.x, fmaf(-c[k], x.y, r[k])) * b[k];
+    for (int k = 1; k <= M - 2; ++k) r[k] = fmaf(-a[k], x.x, fmaf(-c[k], x.y, r[k]));
     r[0] = x.x;
-    r[FM - 1] = x.y;
+    r[M - 1] = x.y;
     __builtin_amdgcn_sched_barrier(0);
 }
 
@@ -217,7 +217,7 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
                 *reinterpret_cast<float4 *>(mine + (q >> 2) * FMP + 4 * (q & 3)) = v[m];
             }
     };
-    float dep[FM + 2], r[FM], a[FM], b[FM], c[FM];
+    float dep[FM + 2], r[FM], a[FM], c[FM];
     put4(vd);
     __syncthreads();
     const float *seg = mine + (row < R ? s : 0) * FMP;
@@ -254,7 +254,7 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
     __syncthreads();
     float3 f;
     float4 l;
-    fs_eliminate(tri_k(d.Bd, d.rdx), i0, d.nx, is_wall(d, 0), is_wall(d, 1), glo, ghi, dep, a, b, c, r, f, l);
+    fs_eliminate<FM>(tri_k(d.Bd, d.rdx), i0, d.nx, is_wall(d, 0), is_wall(d, 1), glo, ghi, dep, a, c, r, f, l);
     float4 vp[4], ve[4];
     auto epilogue_loads = [&] {
 #pragma unroll
@@ -266,7 +266,7 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
     };
     if (EARLY) epilogue_loads();
     const float2 x = fs_reduced(f, l, s, nseg, 1, lds);
-    fs_back(a, b, c, r, x);
+    fs_back(a, c, r, x);
     __syncthreads();
     if (row < R)
 #pragma unroll
@@ -320,12 +320,12 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
     if (__ballot(bad) && (threadIdx.x & 63) == 0) atomicOr(A.health, 1);
 }
 
-template <bool EARLY>
+template <int M, bool EARLY>
 __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T, int g) {
 #pragma clang fp contract(off)
     const Dom &d = A.d;
-    const int nseg = fs_segs(d.ny), C = fs_cols(T, d.ny);
-    const int t = threadIdx.x, s = t / C, i = g * C + (t & (C - 1)), j0 = s * FM;
+    const int nseg = fs_segs(d.ny, M), C = fs_cols(T, d.ny, M);
+    const int t = threadIdx.x, s = t / C, i = g * C + (t & (C - 1)), j0 = s * M;
     const bool live = s < nseg && i < d.nx;
     const int ic = live ? i : 0, jc = live ? j0 : 0, kl = d.ny - 1 - jc;  // kl: the column's last cell
     // one lane offset per field and uniform row offsets (a lane offset per row
@@ -337,71 +337,77 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
     const auto bq = bres(ldp(A.pbase, A.fstride), A.fstride), be = bres(A.eraw, A.fstride);
     const auto bo = bres(ldp(A.pout, A.fstride), A.fstride);
     const unsigned vo = (unsigned)jc * pb + 4u * (unsigned)ic, vz = (unsigned)jc * zb + 4u * (unsigned)ic;
-    float dep[FM + 2], r[FM], a[FM], b[FM], c[FM];
+    float dep[M + 2], r[M], a[M], c[M];
 #pragma unroll
-    for (int k = 0; k < FM; ++k) r[k] = bld(br, vo, k * pb);
+    for (int k = 0; k < M; ++k) r[k] = bld(br, vo, k * pb);
     dep[0] = bld(bd, jc > 0 ? vz - zb : vz, 0);
 #pragma unroll
-    for (int k = 0; k < FM + 1; ++k) dep[k + 1] = bld(bd, vz, k * zb);
+    for (int k = 0; k < M + 1; ++k) dep[k + 1] = bld(bd, vz, k * zb);
     float glo = 0.f, ghi = 0.f, dlo = 0.f, dhi = 0.f;
     const bool lo_wall = is_wall(d, 2), hi_wall = is_wall(d, 3);
     if (!lo_wall && live && s == 0) {
         glo = A.gh1[ghost_index(d, 2, 0, i + 2) + 2] - A.gh0[ghost_index(d, 2, 0, i + 2) + 2];
         dlo = 0.25f * ((d.D[i] + d.D[i + 1]) + (d.D[i] + d.D[i + 1]));
     }
-    if (!hi_wall && live && kl < FM) {
+    if (!hi_wall && live && kl < M) {
         ghi = A.gh1[ghost_index(d, 3, 0, i + 2) + 2] - A.gh0[ghost_index(d, 3, 0, i + 2) + 2];
         const float *Dn = d.D + (size_t)d.ny * d.zpitch;
         dhi = 0.25f * ((Dn[i] + Dn[i + 1]) + (Dn[i] + Dn[i + 1]));
     }
     dep[0] = jc > 0 || lo_wall ? dep[0] : dlo;  // walls: the first and last cells' own depths
 #pragma unroll
-    for (int k = 0; k < FM; ++k) {
+    for (int k = 0; k < M; ++k) {
         const float gd = hi_wall ? dep[k + 1] : dhi;
         dep[k + 2] = k < kl ? dep[k + 2] : gd;
         r[k] = k <= kl ? r[k] : 0.f;
     }
 #pragma unroll
-    for (int k = 0; k < FM + 2; ++k) dep[k] = fmaxf(dep[k], 0.f);
+    for (int k = 0; k < M + 2; ++k) dep[k] = fmaxf(dep[k], 0.f);
     float3 f;
     float4 l;
-    fs_eliminate(tri_k(d.Bd, d.rdy), jc, d.ny, is_wall(d, 2), is_wall(d, 3), glo, ghi, dep, a, b, c, r, f, l);
-    float vq[FM], ve[FM], vd[FM];
-    auto epilogue_loads = [&] {
+    fs_eliminate<M>(tri_k(d.Bd, d.rdy), jc, d.ny, lo_wall, hi_wall, glo, ghi, dep, a, c, r, f, l);
+    // the epilogue goes EP rows at a time
+    constexpr int EP = 16;
+    float vq[EP], ve[EP], vd[EP];
+    auto epilogue_loads = [&](int k0) {
 #pragma unroll
-        for (int k = 0; k < FM; ++k) {
-            vq[k] = bld(bq, vo, k * pb);
-            ve[k] = bld(be, vo, k * pb);
-            vd[k] = bld(bd, vz, k * zb);
+        for (int k = 0; k < EP; ++k) {
+            vq[k] = bld(bq, vo, (k0 + k) * pb);
+            ve[k] = bld(be, vo, (k0 + k) * pb);
+            vd[k] = bld(bd, vz, (k0 + k) * zb);
         }
     };
-    if (EARLY) epilogue_loads();
+    if (EARLY) epilogue_loads(0);
     const float2 x = fs_reduced(f, l, s, nseg, C, lds);
     if (!live) return;
-    fs_back(a, b, c, r, x);
-    if (!EARLY) epilogue_loads();
-#pragma unroll
-    for (int k = 0; k < FM; ++k) r[k] = shore(vq[k] + r[k], ve[k], vd[k], d.eps);
-    if (A.sponge) {
-        const float gx = A.Dc[(size_t)d.ny * d.zpitch + i];
-        float gy[FM];
-#pragma unroll
-        for (int k = 0; k < FM; ++k) gy[k] = ldo(A.Dc, (unsigned)min(jc + k, d.ny - 1) * zb + 4u * (unsigned)d.nx);
-#pragma unroll
-        for (int k = 0; k < FM; ++k) r[k] *= vd[k] > 0.f ? gx * gy[k] : 1.f;
-    }
-    // all values before the first store: left to itself the compiler moves
-    // each row's loads and arithmetic under its store's condition, sixteen
-    // round trips to memory in a row
-#pragma unroll
-    for (int k = 0; k < FM; ++k) asm volatile("" : "+v"(r[k]));
+    fs_back(a, c, r, x);
+    const float gx = A.sponge ? A.Dc[(size_t)d.ny * d.zpitch + i] : 1.f;
     int bad = 0;
 #pragma unroll
-    for (int k = 0; k < FM; ++k)
-        if (k <= kl) {
-            bad |= !isfinite(r[k]);
-            bst(bo, vo, k * pb, r[k]);
+    for (int k0 = 0; k0 < M; k0 += EP) {
+        if (!EARLY || k0 > 0) epilogue_loads(k0);
+#pragma unroll
+        for (int k = 0; k < EP; ++k) r[k0 + k] = shore(vq[k] + r[k0 + k], ve[k], vd[k], d.eps);
+        if (A.sponge) {
+            float gy[EP];
+#pragma unroll
+            for (int k = 0; k < EP; ++k)
+                gy[k] = ldo(A.Dc, (unsigned)min(jc + k0 + k, d.ny - 1) * zb + 4u * (unsigned)d.nx);
+#pragma unroll
+            for (int k = 0; k < EP; ++k) r[k0 + k] *= vd[k] > 0.f ? gx * gy[k] : 1.f;
         }
+        // all values before the first store: left to itself the compiler moves
+        // each row's loads and arithmetic under its store's condition, sixteen
+        // round trips to memory in a row
+#pragma unroll
+        for (int k = 0; k < EP; ++k) asm volatile("" : "+v"(r[k0 + k]));
+#pragma unroll
+        for (int k = 0; k < EP; ++k)
+            if (k0 + k <= kl) {
+                bad |= !isfinite(r[k0 + k]);
+                bst(bo, vo, (k0 + k) * pb, r[k0 + k]);
+            }
+    }
     // lanes that left are not in the vote; one lane of those here reports
     const unsigned long long v = __ballot(bad);
     if (v && (int)(threadIdx.x & 63) == __ffsll((long long)v) - 1) atomicOr(A.health, 1);
@@ -409,28 +415,39 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
 
 // Row workgroups first, then column workgroups, neighbours of which share
 // 128-byte lines: consecutive ones to one XCD.
-template <bool EARLY>
+template <bool EARLY, bool TALL = false>
 __device__ __forceinline__ void solve_body(const SolveArgs &A, float *lds, int b) {
     const int T = blockDim.x, nr = fs_row_groups(T, A.d.nx, A.d.ny), nc = fs_col_groups(T, A.d.nx, A.d.ny);
     if (b < nr) {
         if (b * fs_rows(T, A.d.nx) < A.d.ny) solve_rows<EARLY>(A, lds, T, b);
+    } else if (TALL && A.d.ny > FS_TALL) {
+        solve_cols<FMT, false>(A, lds, T, xcd_order(b - nr, nc));
     } else {
-        solve_cols<EARLY>(A, lds, T, xcd_order(b - nr, nc));
+        solve_cols<FM, EARLY>(A, lds, T, xcd_order(b - nr, nc));
     }
 }
 
 // Up to FS_EARLY threads the registers suffice to have the epilogue's loads in
 // flight across the reduction, which a small grid's few waves need: 128 x 64
-// cells 10.5 -> 9.8 us, 1024 x 512 12.8 -> 12.3.  Larger workgroups load
-// late: 93 registers a lane, five waves a SIMD.
+// cells 10.5 -> 9.8 us, 1024 x 512 12.8 -> 12.3.  Larger workgroups load late.
 constexpr int FS_EARLY = 512;
-__global__ __launch_bounds__(FS_EARLY) __attribute__((amdgpu_waves_per_eu(2))) void k_solve(SolveArgs A) {
+__global__ __launch_bounds__(FS_EARLY) __attribute__((amdgpu_waves_per_eu(4))) void k_solve(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
     solve_body<true>(A, fs_buf, blockIdx.x);
 }
 __global__ __launch_bounds__(1024) void k_solve_big(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
     solve_body<false>(A, fs_buf, blockIdx.x);
+}
+// Columns of more than FS_TALL cells fill a CU's registers with one workgroup,
+// so the rows get a launch of their own, with small workgroups.
+__global__ __launch_bounds__(1024) void k_solve_rows(SolveArgs A) {
+    extern __shared__ __align__(16) float fs_buf[];
+    solve_rows<false>(A, fs_buf, blockDim.x, blockIdx.x);
+}
+__global__ __launch_bounds__(1024) void k_solve_cols(SolveArgs A) {
+    extern __shared__ __align__(16) float fs_buf[];
+    solve_cols<FMT, false>(A, fs_buf, blockDim.x, xcd_order(blockIdx.x, gridDim.x));
 }
 
 }  // namespace ws
