@@ -217,17 +217,14 @@ __device__ __forceinline__ float cell_Dc(const Dom &d, int i, int j) {
     return 0.25f * ((r0[i] + r0[i + 1]) + (r1[i] + r1[i + 1]));
 }
 
-// What the one-kernel solve reads of the cells: still-water depths, and in the
-// spare last column and row of that field the sponge factors of the rows and
-// of the columns.
+// What the one-kernel solve reads of the cells, in the panel layout of nx + 1
+// columns: still-water depths, and in the last column the sponge factors of
+// the rows; those of the columns follow at ny rows of zpitch.
 __global__ void k_cells(Dom d, float *out) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x, j = blockIdx.y;
     if (i > d.nx || j > d.ny) return;
-    float v;
-    if (i < d.nx && j < d.ny) v = cell_Dc(d, i, j);
-    else if (j < d.ny) v = sponge_y(d, j);
-    else v = i < d.nx ? sponge_x(d, i) : 1.f;
-    out[(size_t)j * d.zpitch + i] = v;
+    if (j == d.ny) out[(size_t)j * d.zpitch + i] = i < d.nx ? sponge_x(d, i) : 1.f;
+    else out[panel(i, j, d.ny)] = i < d.nx ? cell_Dc(d, i, j) : sponge_y(d, j);
 }
 
 // Lake at rest: eta = max(0, -D_cell) (surface at still water or on the bottom).

@@ -107,6 +107,13 @@ __device__ inline void wave_eval(const SideDev &s, double x, double y, double t,
     q = sq;
 }
 
+// Panel layout: eight columns side by side, row after row, then the next eight
+// (float index of column i, row j of an ny-row field).  A workgroup that takes
+// eight whole columns reads one contiguous run of memory.
+__device__ __forceinline__ unsigned panel(int i, int j, int ny) {
+    return ((unsigned)(i >> 3) * (unsigned)ny + (unsigned)j) * 8u + (unsigned)(i & 7);
+}
+
 // Value of cell (i, j), inside or in the two-cell ghost ring: reflected across
 // every wall side first (normal discharge of that side changes sign), then, if
 // still behind a wave-maker side, that maker's values at the reflected

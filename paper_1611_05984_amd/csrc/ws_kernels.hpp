@@ -383,7 +383,7 @@ __device__ __forceinline__ void stencil_body(const StencilArgs &A, int bx, int b
                     U = shore((kind == 2 ? Pnv : p1) + U, en, Dc, eps);
                     V = shore((kind == 2 ? Qnv : q1) + V, en, Dc, eps);
                     if ((A.flags & F_SPONGE) && Dc > 0.f) {
-                        const float gm = gcol * A.cells[(size_t)u * d.zpitch + d.nx];
+                        const float gm = gcol * A.cells[panel(d.nx, u, d.ny)];
                         en *= gm;
                         U *= gm;
                         V *= gm;
@@ -467,7 +467,8 @@ struct SolveArgs {
     Dom d;
     float *rx;                 // right-hand sides: pairs packed per cell (reduction and
                                // expansion), or two fields (one-kernel solve)
-    const float *Dc;           // cell still-water depth (unclamped), rows of zpitch (one-kernel solve)
+    const float *Dc;           // cell field of the one-kernel solve (k_cells): unclamped still-water
+                               // depths and row sponge factors in the panel layout, column factors
     float4 *redx, *redy;       // reduced equations (sub, diag, super, rhs) per unknown
     float *solx, *soly;        // reduced solutions
     // layout 1 (factored solve): the reduced right-hand sides (in the memory of

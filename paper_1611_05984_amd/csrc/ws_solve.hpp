@@ -184,14 +184,15 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
     const int nseg = fs_segs(d.nx), R = fs_rows(T, d.nx);
     const int t = threadIdx.x, row = t / nseg, s = t - row * nseg, j = g * R + row;
     const bool live = row < R && j < d.ny;
-    const size_t o = (size_t)(live ? j : 0) * d.pitch, oz = (size_t)(live ? j : 0) * d.zpitch;
+    const int jl = live ? j : 0;
+    const size_t o = (size_t)jl * d.pitch, oz = (size_t)jl * d.zpitch;
     // coalesced: thread (row, s) moves 16 bytes at cells 4 (s + m nseg)
     float4 vr[4], vd[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
         const int q = 4 * (s + m * nseg);
         vr[m] = live ? *reinterpret_cast<const float4 *>(A.rx + o + q) : make_float4(0.f, 0.f, 0.f, 0.f);
-        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + oz + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + panel(q, jl, d.ny)) : make_float4(0.f, 0.f, 0.f, 0.f);
         // padding past the row's end is never written: whatever it holds must not spread
         vr[m].x = q < d.nx ? vr[m].x : 0.f;
         vr[m].y = q + 1 < d.nx ? vr[m].y : 0.f;
@@ -274,11 +275,11 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
             *reinterpret_cast<float4 *>(const_cast<float *>(seg) + k) = make_float4(r[k], r[k + 1], r[k + 2], r[k + 3]);
     if (!EARLY) epilogue_loads();
     const float *gx = A.Dc + (size_t)d.ny * d.zpitch;  // sponge factors of the columns
-    const float gy = A.sponge && live ? A.Dc[oz + d.nx] : 1.f;
+    const float gy = A.sponge && live ? A.Dc[panel(d.nx, jl, d.ny)] : 1.f;
 #pragma unroll
     for (int m = 0; m < 4; ++m) {
         const int q = 4 * (s + m * nseg);
-        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + oz + q) : make_float4(0.f, 0.f, 0.f, 0.f);
+        vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + panel(q, jl, d.ny)) : make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
     int bad = 0;
@@ -328,21 +329,20 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
     const int t = threadIdx.x, s = t / C, i = g * C + (t & (C - 1)), j0 = s * M;
     const bool live = s < nseg && i < d.nx;
     const int ic = live ? i : 0, jc = live ? j0 : 0, kl = d.ny - 1 - jc;  // kl: the column's last cell
-    // one lane offset per field and uniform row offsets (a lane offset per row
-    // cost 34 registers); the fields hold whole segments of rows, the depth
-    // one row past the last and then other data: what lies past the end is
-    // replaced
-    const unsigned pb = 4u * (unsigned)d.pitch, zb = 4u * (unsigned)d.zpitch;
-    const auto br = bres(ldp(A.rx, A.fstride), A.fstride), bd = bres(A.Dc, zb * (unsigned)d.ny);
+    // one lane offset per layout and uniform row offsets (a lane offset per row
+    // cost 34 registers); what lies past the column's end is other data of
+    // the workspace, and replaced
+    const unsigned pb = 4u * (unsigned)d.pitch;
+    const auto br = bres(ldp(A.rx, A.fstride), A.fstride), bd = bres(A.Dc, 4u * (unsigned)d.zpitch * (unsigned)(d.ny + 1));
     const auto bq = bres(ldp(A.pbase, A.fstride), A.fstride), be = bres(A.eraw, A.fstride);
     const auto bo = bres(ldp(A.pout, A.fstride), A.fstride);
-    const unsigned vo = (unsigned)jc * pb + 4u * (unsigned)ic, vz = (unsigned)jc * zb + 4u * (unsigned)ic;
+    const unsigned vo = (unsigned)jc * pb + 4u * (unsigned)ic, vp = 4u * panel(ic, jc, d.ny);
     float dep[M + 2], r[M], a[M], c[M];
 #pragma unroll
     for (int k = 0; k < M; ++k) r[k] = bld(br, vo, k * pb);
-    dep[0] = bld(bd, jc > 0 ? vz - zb : vz, 0);
+    dep[0] = bld(bd, jc > 0 ? vp - 32u : vp, 0);
 #pragma unroll
-    for (int k = 0; k < M + 1; ++k) dep[k + 1] = bld(bd, vz, k * zb);
+    for (int k = 0; k < M + 1; ++k) dep[k + 1] = bld(bd, vp + 32u * k, 0);
     float glo = 0.f, ghi = 0.f, dlo = 0.f, dhi = 0.f;
     const bool lo_wall = is_wall(d, 2), hi_wall = is_wall(d, 3);
     if (!lo_wall && live && s == 0) {
@@ -374,7 +374,7 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
         for (int k = 0; k < EP; ++k) {
             vq[k] = bld(bq, vo, (k0 + k) * pb);
             ve[k] = bld(be, vo, (k0 + k) * pb);
-            vd[k] = bld(bd, vz, (k0 + k) * zb);
+            vd[k] = bld(bd, vp + 32u * (k0 + k), 0);
         }
     };
     if (EARLY) epilogue_loads(0);
@@ -392,7 +392,7 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
             float gy[EP];
 #pragma unroll
             for (int k = 0; k < EP; ++k)
-                gy[k] = ldo(A.Dc, (unsigned)min(jc + k0 + k, d.ny - 1) * zb + 4u * (unsigned)d.nx);
+                gy[k] = A.Dc[panel(d.nx, min(jc + k0 + k, d.ny - 1), d.ny)];
 #pragma unroll
             for (int k = 0; k < EP; ++k) r[k0 + k] *= vd[k] > 0.f ? gx * gy[k] : 1.f;
         }
@@ -413,13 +413,15 @@ __device__ __forceinline__ void solve_cols(const SolveArgs &A, float *lds, int T
     if (v && (int)(threadIdx.x & 63) == __ffsll((long long)v) - 1) atomicOr(A.health, 1);
 }
 
-// Row workgroups first, then column workgroups, neighbours of which share
-// 128-byte lines: consecutive ones to one XCD.
+// Row workgroups first, then column workgroups.  Consecutive ones go to one
+// XCD: neighbouring columns share 128-byte lines of the row-major fields,
+// neighbouring rows those of the depth panels.
 template <bool EARLY, bool TALL = false>
 __device__ __forceinline__ void solve_body(const SolveArgs &A, float *lds, int b) {
     const int T = blockDim.x, nr = fs_row_groups(T, A.d.nx, A.d.ny), nc = fs_col_groups(T, A.d.nx, A.d.ny);
     if (b < nr) {
-        if (b * fs_rows(T, A.d.nx) < A.d.ny) solve_rows<EARLY>(A, lds, T, b);
+        const int g = xcd_order(b, nr);
+        if (g * fs_rows(T, A.d.nx) < A.d.ny) solve_rows<EARLY>(A, lds, T, g);
     } else if (TALL && A.d.ny > FS_TALL) {
         solve_cols<FMT, false>(A, lds, T, xcd_order(b - nr, nc));
     } else {
@@ -443,7 +445,7 @@ __global__ __launch_bounds__(1024) void k_solve_big(SolveArgs A) {
 // so the rows get a launch of their own, with small workgroups.
 __global__ __launch_bounds__(1024) void k_solve_rows(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
-    solve_rows<false>(A, fs_buf, blockDim.x, blockIdx.x);
+    solve_rows<false>(A, fs_buf, blockDim.x, xcd_order(blockIdx.x, gridDim.x));
 }
 __global__ __launch_bounds__(1024) void k_solve_cols(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
