@@ -95,7 +95,7 @@ static ws_status busy_check(const ws_domain *d, const char *who) {
     if (d->batch && d->stale) return fail(WS_EBUSY, "%s: domain advanced by its batch; call ws_batch_sync first", who);
     return WS_OK;
 }
-static void batch_touch(ws_domain *d);
+static void batch_touch(ws_domain *d, bool args = true);
 
 static size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 static int roundup(int x, int m) { return (x + m - 1) / m * m; }
@@ -784,6 +784,7 @@ extern "C" size_t ws_snapshot_bytes_grid(const ws_grid *g) {
     return 256 + 18 * sizeof(float) * (size_t)L.nyp * L.pitch + sizeof(float) * (size_t)(g->ny + 1) * L.zpitch;
 }
 
+static_assert(TX * TY * sizeof(float) % 256 == 0, "a field of whole tiles fills its 256-byte aligned stride");
 static size_t snap_field_bytes(const ws_domain *d) { return sizeof(float) * (size_t)d->nyp * d->pitch; }
 static size_t snap_corner_bytes(const ws_domain *d) { return sizeof(float) * (size_t)(d->g.ny + 1) * d->zpitch; }
 
@@ -813,9 +814,12 @@ extern "C" ws_status ws_snapshot(ws_domain *d, void *dst_dev, size_t bytes, void
     char *p = (char *)dst_dev;
     hipLaunchKernelGGL(k_snap_header, dim3(1), dim3(64), 0, st, h, (SnapHeader *)p);
     p += 256;
-    for (int f = 0; f < 3; ++f, p += fb) HIPCHK(hipMemcpyAsync(p, d->st[d->cur][f], fb, hipMemcpyDeviceToDevice, st));
-    for (int sl = 0; sl < 3; ++sl)
-        for (int f = 0; f < 5; ++f, p += fb) HIPCHK(hipMemcpyAsync(p, d->hist[sl][f], fb, hipMemcpyDeviceToDevice, st));
+    // a field fills its stride (rows of whole tiles), so the fields of a group
+    // are copied as one: 3 copies, not 19 (5 us each at the smallest sizes)
+    HIPCHK(hipMemcpyAsync(p, d->st[d->cur][0], 3 * fb, hipMemcpyDeviceToDevice, st));
+    p += 3 * fb;
+    HIPCHK(hipMemcpyAsync(p, d->hist[0][0], 15 * fb, hipMemcpyDeviceToDevice, st));
+    p += 15 * fb;
     HIPCHK(hipMemcpyAsync(p, d->D, cb, hipMemcpyDeviceToDevice, st));
     HIPCHK(hipGetLastError());
     return WS_OK;
@@ -834,9 +838,10 @@ extern "C" ws_status ws_restore(ws_domain *d, const void *src_dev, size_t bytes,
         h.zpitch != d->zpitch || h.total != need || h.n_corr != d->g.n_corr || h.model != d->g.model)
         return fail(WS_EINVAL, "ws_restore: snapshot does not match this domain's grid");
     const char *p = (const char *)src_dev + 256;
-    for (int f = 0; f < 3; ++f, p += fb) HIPCHK(hipMemcpyAsync(d->st[0][f], p, fb, hipMemcpyDeviceToDevice, st));
-    for (int sl = 0; sl < 3; ++sl)
-        for (int f = 0; f < 5; ++f, p += fb) HIPCHK(hipMemcpyAsync(d->hist[sl][f], p, fb, hipMemcpyDeviceToDevice, st));
+    HIPCHK(hipMemcpyAsync(d->st[0][0], p, 3 * fb, hipMemcpyDeviceToDevice, st));
+    p += 3 * fb;
+    HIPCHK(hipMemcpyAsync(d->hist[0][0], p, 15 * fb, hipMemcpyDeviceToDevice, st));
+    p += 15 * fb;
     HIPCHK(hipMemcpyAsync(d->D, p, cb, hipMemcpyDeviceToDevice, st));
     refresh_cells(d, st);
     HIPCHK(hipMemsetAsync(d->health, 0, sizeof(int), st));
@@ -846,8 +851,8 @@ extern "C" ws_status ws_restore(ws_domain *d, const void *src_dev, size_t bytes,
     // the multistep history restarts (two Euler steps), as after a change of dt
     d->step = h.dt == d->g.dt ? h.step : 0;
     d->t = h.t;
-    d->lu_valid = false;  // bathymetry restored
-    batch_touch(d);
+    d->lu_valid = false;  // bathymetry restored (in place: the argument tables hold)
+    batch_touch(d, false);
     return WS_OK;
 }
 
@@ -861,7 +866,7 @@ extern "C" ws_status ws_set_state(ws_domain *d, const float *w, const float *P, 
     HIPCHK(hipGetLastError());
     d->t = t;
     d->step = 0;
-    batch_touch(d);
+    batch_touch(d, false);
     return WS_OK;
 }
 
@@ -1418,9 +1423,11 @@ static size_t batch_layout(int max, size_t *o_state, size_t *o_pre) {
     return a + b + 6 * c;
 }
 
-static void batch_touch(ws_domain *d) {
+// The batch must upload the domain's step, time and state buffer again, and
+// (args) its pass argument tables: anything but a new state changes those.
+static void batch_touch(ws_domain *d, bool args) {
     if (!d) return;
-    d->vdirty = true;
+    if (args) d->vdirty = true;
     if (d->batch) d->batch->dirty = true;
 }
 
@@ -1457,8 +1464,10 @@ static BatchDesc make_desc(const ws_domain *d, int sy) {
 
 // Pass argument tables of one domain (device), in the order of variant().
 static ws_status write_vtab(ws_domain *d) {
-    std::vector<StencilArgs> sa(d->nvar);
-    std::vector<SolveArgs> so(d->nvar);
+    // the two tables lie one after the other: one copy
+    std::vector<char> img((sizeof(StencilArgs) + sizeof(SolveArgs)) * d->nvar);
+    StencilArgs *sa = reinterpret_cast<StencilArgs *>(img.data());
+    SolveArgs *so = reinterpret_cast<SolveArgs *>(sa + d->nvar);
     const Dom m = make_dom(d);
     for (int key = 0; key < 9; ++key) {
         const int cur = key / 3, sm = key % 3;
@@ -1468,8 +1477,7 @@ static ws_status write_vtab(ws_domain *d) {
             pass_args(d, m, false, cur, sm, p, sa[v], so[v], true, true);
         }
     }
-    HIPCHK(hipMemcpy(d->vsa, sa.data(), sizeof(StencilArgs) * d->nvar, hipMemcpyHostToDevice));
-    HIPCHK(hipMemcpy(d->vso, so.data(), sizeof(SolveArgs) * d->nvar, hipMemcpyHostToDevice));
+    HIPCHK(hipMemcpy(d->vsa, img.data(), img.size(), hipMemcpyHostToDevice));
     d->vdirty = false;
     return WS_OK;
 }
@@ -1554,10 +1562,15 @@ static ws_status batch_upload(ws_batch *b) {
         maxK = D.K > maxK ? D.K : maxK;
     }
     if (n) {
-        HIPCHK(hipMemcpy(b->d_desc, desc.data(), sizeof(BatchDesc) * n, hipMemcpyHostToDevice));
-        HIPCHK(hipMemcpy(b->d_state, b->h_state.data(), sizeof(BatchState) * n, hipMemcpyHostToDevice));
-        for (int q = 0; q < 6; ++q)
-            HIPCHK(hipMemcpy(b->d_pre[q], pre[q].data(), sizeof(int) * (n + 1), hipMemcpyHostToDevice));
+        // one copy of the whole (small) batch workspace instead of eight: each
+        // waits for the device, some 20 us
+        size_t o_state, o_pre;
+        std::vector<char> img(batch_layout(b->max, &o_state, &o_pre));
+        std::memcpy(img.data(), desc.data(), sizeof(BatchDesc) * n);
+        std::memcpy(img.data() + o_state, b->h_state.data(), sizeof(BatchState) * n);
+        const size_t c = align256(sizeof(int) * (size_t)(b->max + 1));
+        for (int q = 0; q < 6; ++q) std::memcpy(img.data() + o_pre + q * c, pre[q].data(), sizeof(int) * (n + 1));
+        HIPCHK(hipMemcpy(b->d_desc, img.data(), img.size(), hipMemcpyHostToDevice));
     }
     bool same = n == (int)b->order.size() && maxK == b->maxK && nred == b->nred && b->rp == rp0 && b->rc == rc0 &&
                 fsT == b->fsT && tall == b->tall && models[0] == b->models[0] && models[1] == b->models[1];
