@@ -79,7 +79,7 @@ struct ws_domain {
     int sy, pnt, solver;           // tuning: stencil rows per strip, PCR threads per system, reduced solver
     int syc;                       // stencil rows per strip in corrector passes (0: sy)
     bool fs_zero[3];               // history slots whose F*, G* are known to be zero (NLSW steps)
-    bool rows_set;                 // the heights above are the caller's (else short_rows() picks)
+    int rows_by;                   // who chose the heights above (ROWS_*)
     size_t fstride;                // bytes between consecutive fields
     StencilArgs *vsa;              // pass argument tables (device), batch use only
     SolveArgs *vso;
@@ -90,6 +90,12 @@ struct ws_domain {
     double last_dw, last_dpq;      // changes measured after the last corrector
     int static_dev;                // device whose static array holds the workspace (-1: the caller's)
 };
+
+// Heights nobody chose follow short_rows(); so does the autotuner's 8.
+enum { ROWS_NOBODY = 0, ROWS_CALLER = 1, ROWS_TUNER = 2 };
+static int height(int nominal, int by, int rule) {
+    return by == ROWS_NOBODY || (by == ROWS_TUNER && nominal == 8) ? rule : nominal;
+}
 
 static ws_status busy_check(const ws_domain *d, const char *who) {
     if (d->batch && d->stale) return fail(WS_EBUSY, "%s: domain advanced by its batch; call ws_batch_sync first", who);
@@ -969,27 +975,24 @@ static dim3 strips_for(const ws_domain *d, int sy, bool solo = false) {
 }
 
 // Strip height where the caller chose none (or the autotuner its shortest).
-// One wave walks a strip row by row, 1.4 us a row when it has its SIMD to
-// itself, after three warm-up rows; a shorter strip repeats more warm-up rows
-// but starts more waves.  So: the shortest of 1, 2, 4 and 8 rows that keeps
-// the launch within about three waves a SIMD (3200), 8 where none does.
-// Measured, us a step with rows of 32 / 8 / 4 / 2 / 1: 128 x 64 cells (192
-// waves at 1 row) 188 / 93 / 79 / 73 / 64; 601 x 601 (3005 at 2) 210 / 109 /
-// 97 / 95 / 100; 1024 x 512 (2176 at 4) 257 / 133 / 113 / 115 / 123;
-// 2048 x 1500 431 / 340 / 335 / 356 / 404.  Heights give the same bits.
+// One wave walks a strip row by row after three warm-up rows; a shorter strip
+// repeats more warm-up rows, from cache, but starts more waves, and up to two
+// rows the loop is unrolled.  1 row while its waves fit the chip at once, 2 up
+// to about 9 million cells, beyond that 8: there the repeated rows go to
+// memory.  Measured, us a step with rows of 8 / 4 / 2 / 1: 128 x 64 cells (192
+// waves at 1 row) 71 / 49 / 42 / 38; 2000 x 65 (2145) 90 / 66 / 57 / 51; 601 x
+// 601 (6010) 82 / 64 / 56 / 58; 1024 x 1024 116 / 109 / 102 / 103; 2048 x 1500
+// 259 / 257 / 245 / 254; 2048 x 2048 329 / 329 / 317 / 331; 3000 x 3000 (73500
+// at 2) 709 / 721 / 714 / 744; 4096 x 4096 1257 / 1306 / 1305 / 1356.  Heights
+// give the same bits.
 static long strip_waves(int nx, int ny, int sy) { return (long)((nx + SO - 1) / SO) * ((ny + sy - 1) / sy); }
-static constexpr long SHORT_WAVES = 3200;
-static int short_rows(int nx, int ny) {
-    int r = 1;
-    while (r < 8 && strip_waves(nx, ny, r) > SHORT_WAVES) r *= 2;
-    return r;
-}
+static int rows_for(long waves1, long waves2) { return waves1 <= 4096 ? 1 : waves2 <= 72000 ? 2 : 8; }
+static int short_rows(int nx, int ny) { return rows_for(strip_waves(nx, ny, 1), strip_waves(nx, ny, 2)); }
 
 #define SY_SWITCH(K, sy, LAUNCH)                        \
     do {                                                \
         if (sy == 1) LAUNCH(K<1>);                      \
         else if (sy == 2) LAUNCH(K<2>);                 \
-        else if (sy == 4) LAUNCH(K<4>);                 \
         else if (sy == 8) LAUNCH(K<8>);                 \
         else if (sy == 16) LAUNCH(K<16>);               \
         else if (sy == 24) LAUNCH(K<24>);               \
@@ -1263,7 +1266,7 @@ static void launch_solves(ws_domain *d, const SolveArgs &so, hipStream_t st) {
 static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st) {
     {
         ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
-        const int rows = !d->rows_set ? short_rows(d->g.nx, d->g.ny) : sa.kind == 2 && d->syc ? d->syc : d->sy;
+        const int rows = height(sa.kind == 2 && d->syc ? d->syc : d->sy, d->rows_by, short_rows(d->g.nx, d->g.ny));
         launch_stencil(d, rows, st, sa);
     }
     launch_solves(d, so, st);
@@ -1395,23 +1398,22 @@ struct ws_batch {
     hipStream_t last = nullptr;
     int sy = SY, pnt = PCR_NT, solver = WS_SOLVE_PCR;  // tuning shared by all domains of the batch
     int syc = 0;                                        // corrector-pass stencil rows (0: sy)
-    bool rows_set = false;                              // the heights are the caller's (else batch_rows() picks)
+    int rows_by = ROWS_NOBODY;                          // who chose the heights
     int rp = SY, rc = SY;                               // heights the tables were built for
 };
 
 // Strip heights of the batch: the caller's or the autotuner's, else by the
 // rule of short_rows() on the waves of all its domains together.
 static void batch_rows(ws_batch *b, const std::vector<int> &order) {
-    b->rp = b->sy;
-    b->rc = b->syc ? b->syc : b->sy;
-    if (b->rows_set) return;
-    int r = 1;
-    for (; r < 8; r *= 2) {
-        long waves = 0;
-        for (int sl : order) waves += strip_waves(b->slots[sl]->g.nx, b->slots[sl]->g.ny, r);
-        if (waves <= SHORT_WAVES) break;
+    long w1 = 0, w2 = 0;
+    for (int sl : order) {
+        const ws_grid &g = b->slots[sl]->g;
+        w1 += strip_waves(g.nx, g.ny, 1);
+        w2 += strip_waves(g.nx, g.ny, 2);
     }
-    b->rp = b->rc = r;
+    const int rule = rows_for(w1, w2);
+    b->rp = height(b->sy, b->rows_by, rule);
+    b->rc = height(b->syc ? b->syc : b->sy, b->rows_by, rule);
 }
 
 static size_t batch_layout(int max, size_t *o_state, size_t *o_pre) {
@@ -1824,7 +1826,7 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
                     nred_of(d));
     d->sy = t->stencil_rows;
     d->syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
-    d->rows_set = true;
+    d->rows_by = ROWS_CALLER;
     d->pnt = t->pcr_threads;
     if (d->solver != t->solver) batch_touch(d);  // argument blocks carry the solve layout
     d->solver = t->solver;
@@ -1834,12 +1836,12 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
 extern "C" ws_status ws_batch_set_tuning(ws_batch *b, const ws_tuning *t) {
     if (!b || !tuning_ok(t)) return fail(WS_EINVAL, "ws_batch_set_tuning: bad tuning");
     const int syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
-    if (!b->rows_set || b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
+    if (b->rows_by != ROWS_CALLER || b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
         b->sy = t->stencil_rows;
         b->syc = syc;
         b->pnt = t->pcr_threads;
         b->solver = t->solver;
-        b->rows_set = true;
+        b->rows_by = ROWS_CALLER;
         b->dirty = true;
         b->total[0] = -1;  // launch shapes change: the captured step is rebuilt
     }
@@ -1849,7 +1851,7 @@ extern "C" ws_status ws_batch_set_tuning(ws_batch *b, const ws_tuning *t) {
 // The autotuner's choice, applied: its shortest height may be shortened.
 static ws_status set_tuned(ws_domain *d, const ws_tuning *t) {
     const ws_status r = ws_set_tuning(d, t);
-    if (r == WS_OK && d->sy == 8 && d->syc == 0) d->rows_set = false;
+    if (r == WS_OK) d->rows_by = ROWS_TUNER;
     return r;
 }
 
@@ -1922,15 +1924,16 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     const int rows[6] = {8, 16, 24, 32, 48, 64};
     float t_rows[2][6];
     for (int c = 0; c < 6; ++c) t_rows[0][c] = t_rows[1][c] = 1e30f;
+    auto trial = [&](int c) { return height(rows[c], ROWS_TUNER, short_rows(d->g.nx, d->g.ny)); };
     for (int c = 0; c < 6; ++c) {  // warm-up
-        launch_stencil(d, rows[c], st, sp);
-        launch_stencil(d, rows[c], st, sa);
+        launch_stencil(d, trial(c), st, sp);
+        launch_stencil(d, trial(c), st, sa);
     }
     for (int round = 0; round < 3; ++round)
         for (int kind = 0; kind < 2; ++kind)
             for (int c = 0; c < 6; ++c) {
                 HIPCHK(hipEventRecord(e0, st));
-                for (int k = 0; k < reps; ++k) launch_stencil(d, rows[c], st, kind ? sa : sp);
+                for (int k = 0; k < reps; ++k) launch_stencil(d, trial(c), st, kind ? sa : sp);
                 HIPCHK(hipEventRecord(e1, st));
                 HIPCHK(hipEventSynchronize(e1));
                 float ms = 0.f;
@@ -2045,7 +2048,7 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     float best = 1e30f, best_c = 1e30f, tp[6], tc[6];
     for (int c = 0; c < 6; ++c) tp[c] = tc[c] = 1e30f;
     b->syc = 0;
-    b->rows_set = true;
+    b->rows_by = ROWS_TUNER;  // (the 8-row trial runs the rule's height)
     for (int c = 0; c < 6; ++c) {
         b->sy = rows[c];
         b->dirty = true;
@@ -2059,13 +2062,14 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
             ms[p] = time_it([&] {
                 const dim3 sg(b->total[p > 0 ? 4 : 0]);
 #define L5(KERN) hipLaunchKernelGGL(KERN, sg, dim3(p > 0 ? 64 : 64 * SWG), 0, st, b->d_desc, b->d_state, b->d_pre[p > 0 ? 4 : 0], n, p)
+                const int h = p > 0 ? b->rc : b->rp;
                 if (b->models[WS_BSNQ]) {
-                    if (p > 0) SY_SWITCH(kb_stencil_c, b->sy, L5);
-                    else SY_SWITCH(kb_stencil_p, b->sy, L5);
+                    if (p > 0) SY_SWITCH(kb_stencil_c, h, L5);
+                    else SY_SWITCH(kb_stencil_p, h, L5);
                 }
                 if (b->models[WS_NLSW]) {
-                    if (p > 0) SY_SWITCH(kb_nlsw_c, b->sy, L5);
-                    else SY_SWITCH(kb_nlsw_p, b->sy, L5);
+                    if (p > 0) SY_SWITCH(kb_nlsw_c, h, L5);
+                    else SY_SWITCH(kb_nlsw_p, h, L5);
                 }
 #undef L5
             });
@@ -2086,7 +2090,6 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     }
     b->sy = best_sy;
     b->syc = best_syc == best_sy ? 0 : best_syc;
-    if (b->sy == 8 && b->syc == 0) b->rows_set = false;  // the shortest candidate may be shortened
     b->dirty = true;
     if ((r = batch_upload(b)) != WS_OK) return r;
     const int n = (int)b->order.size();

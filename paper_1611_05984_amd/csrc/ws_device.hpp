@@ -192,38 +192,40 @@ struct F3 { float e, n, t; };  // surface, normal and tangential discharge at a 
 // theta > 0, and the face values take half the slope, so the limiter runs on
 // the plain differences with the central one scaled by kc = 1/(2 theta), and
 // the face values add or subtract hth = theta/2 times its result (two
-// multiplies fewer a variable).
-struct Recon { float kc, hth; };
-__device__ __forceinline__ Recon recon_k(float th) { return {0.5f / th, 0.5f * th}; }
-
-// Limited linear reconstruction of one cell along one direction, then the
-// conservative positivity correction of the surface against the depths of
-// the cell's low/high faces (w < B  <=>  eta < -D).
-__device__ __forceinline__ void reconstruct(float em, float e0, float ep, float nm, float n0,
-                                            float np, float tm, float t0, float tp, float Dlo,
-                                            float Dhi, Recon rk, F3 &lo, F3 &hi) {
-    const float me = minmod3(e0 - em, rk.kc * (ep - em), ep - e0);
-    const float mn = minmod3(n0 - nm, rk.kc * (np - nm), np - n0);
-    const float mt = minmod3(t0 - tm, rk.kc * (tp - tm), tp - t0);
-    // explicit fused multiply-adds: theta/2 is not a power of two, so a
-    // multiply and an add would round differently from one fused operation,
-    // and the compiler's choice between the two may differ between kernel
-    // instances (strip heights), which must give the same bits
-    const float lo_e = fmaf(-rk.hth, me, e0), hi_e = fmaf(rk.hth, me, e0);
-    const bool fix_hi = hi_e < -Dhi, fix_lo = !fix_hi && lo_e < -Dlo;
-    lo.e = fix_hi ? 2.f * e0 + Dhi : (fix_lo ? -Dlo : lo_e);
-    hi.e = fix_hi ? -Dhi : (fix_lo ? 2.f * e0 + Dlo : hi_e);
-    lo.n = fmaf(-rk.hth, mn, n0);
-    hi.n = fmaf(rk.hth, mn, n0);
-    lo.t = fmaf(-rk.hth, mt, t0);
-    hi.t = fmaf(rk.hth, mt, t0);
+// multiplies fewer a variable).  thr: the depth eps^(1/4) from which eq. 14 is
+// m / h (kept away from 0, where the reciprocal would be infinite).
+struct Recon { float kc, hth, thr; };
+__device__ __forceinline__ Recon recon_k(float th, float eps) {
+    return {0.5f / th, 0.5f * th, fmaxf(fsqrt(fsqrt(eps)), 1e-9f)};
 }
 
-// Desingularized velocity sqrt(2) h m / sqrt(h^4 + max(h^4, eps)).
-__device__ __forceinline__ float desing(float h, float m, float eps) {
-    float h2 = h * h, h4 = h2 * h2;
-    return 1.41421356237f * h * m * frsq(h4 + fmaxf(h4, eps));
+// All arithmetic from here to the face fluxes is written in explicit fused
+// and separate operations with contraction off: the compiler's choice between
+// the two may differ between kernel instances (strip heights, batch or
+// single), which must give the same bits.
+
+// Limited linear reconstruction of one variable of a cell along one
+// direction: v its value, a and b its differences to the lower and upper
+// neighbour (a row's b is the next row's a).
+__device__ __forceinline__ void face_values(float v, float a, float b, Recon rk, float &lo, float &hi) {
+#pragma clang fp contract(off)
+    const float m = minmod3(a, rk.kc * (a + b), b);
+    lo = fmaf(-rk.hth, m, v);
+    hi = fmaf(rk.hth, m, v);
 }
+
+// Conservative positivity correction of a cell's two face surfaces against
+// the depths of its faces (w < B  <=>  eta < -D).
+__device__ __forceinline__ void keep_positive(float e0, float Dlo, float Dhi, float &lo, float &hi) {
+#pragma clang fp contract(off)
+    const bool fix_hi = hi < -Dhi, fix_lo = !fix_hi && lo < -Dlo;
+    const float l = lo, h = hi;
+    lo = fix_hi ? fmaf(2.f, e0, Dhi) : (fix_lo ? -Dlo : l);
+    hi = fix_hi ? -Dhi : (fix_lo ? fmaf(2.f, e0, Dlo) : h);
+}
+
+// One side of a face: velocities, discharges, wave speed, momentum flux.
+struct FaceSide { float u, v, n, t, c, F; };
 
 // Central-upwind flux at a face in well-balanced ("pre-balanced") form.  With
 // D_f the face still-water depth and h = eta + D_f, the pressure g h^2/2 is
@@ -232,29 +234,57 @@ __device__ __forceinline__ float desing(float h, float m, float eps) {
 // the matching part of the bottom source, so it is dropped here and the
 // source becomes g (D_hi - D_lo)/dx * eta_cell.  Where both sides are dry the
 // face flux of the original form is zero, i.e. (0, -g D_f^2/2, 0) here.
+// With the weight w = a+/(a+ - a-) the average (a+ X_L - a- X_R)/(a+ - a-) is
+// X_R + w (X_L - X_R), and the diffusion's a+ a-/(a+ - a-) is w a-.
+// wet (uniform over the wave): both sides of every lane's face are at least
+// thr deep, where eq. 14 gives u = m / h, the discharges themselves, and no
+// case of the general form below applies: 44 operations instead of about 85
+// for most waves of most grids.  A lane's own result does not depend on which
+// of the two forms its wave took.
 // Returns (mass, normal momentum, tangential momentum).
-__device__ __forceinline__ void cu_flux(float g, float eps, float Df, const F3 &L, const F3 &R,
+__device__ __forceinline__ void cu_flux(bool wet, float g, float eps, float thr, float Df, const F3 &L, const F3 &R,
                                         float &H0, float &H1, float &H2) {
-    const float hL = fmaxf(L.e + Df, 0.f), hR = fmaxf(R.e + Df, 0.f);
-    const float hL2 = hL * hL, hL4 = hL2 * hL2, hR2 = hR * hR, hR4 = hR2 * hR2;
-    // eq. (14): u = m * sqrt(2) h / sqrt(h^4 + max(h^4, eps)), one factor per side
-    const float fL = 1.41421356237f * hL * frsq(hL4 + fmaxf(hL4, eps));
-    const float fR = 1.41421356237f * hR * frsq(hR4 + fmaxf(hR4, eps));
-    const float uL = fL * L.n, vL = fL * L.t, uR = fR * R.n, vR = fR * R.t;
-    const float nL = hL * uL, tL = hL * vL, nR = hR * uR, tR = hR * vR;
-    const float cL = fsqrt(g * hL), cR = fsqrt(g * hR);
-    const float ap = fmaxf(fmaxf(uL + cL, uR + cR), 0.f);
-    const float am = fminf(fminf(uL - cL, uR - cR), 0.f);
-    const float eL = hL > 0.f ? L.e : -Df, eR = hR > 0.f ? R.e : -Df;
-    const float pL = 0.5f * g * eL * (eL + 2.f * Df), pR = 0.5f * g * eR * (eR + 2.f * Df);
-    const bool dry = ap - am <= 1e-10f;
-    const float inv = frcp(dry ? 1.f : ap - am), apam = ap * am * inv;
-    const float m = (ap * nL - am * nR) * inv + apam * (R.e - L.e);
-    const float n = (ap * (nL * uL + pL) - am * (nR * uR + pR)) * inv + apam * (nR - nL);
-    const float t = (ap * (nL * vL) - am * (nR * vR)) * inv + apam * (tR - tL);
-    H0 = dry ? 0.f : m;
-    H1 = dry ? -0.5f * g * Df * Df : n;
-    H2 = dry ? 0.f : t;
+#pragma clang fp contract(off)
+    const float hg = 0.5f * g, hL = L.e + Df, hR = R.e + Df;
+    FaceSide l, r;
+    float am, ap, inv;
+    bool dry = false;
+    if (wet) {
+        auto side = [&](float h, const F3 &s) -> FaceSide {
+            const float f = frcp(h), u = f * s.n;
+            return {u, f * s.t, s.n, s.t, fsqrt(g * h), fmaf(hg * s.e, fmaf(2.f, Df, s.e), s.n * u)};
+        };
+        l = side(hL, L);
+        r = side(hR, R);
+        ap = fmaxf(fmaxf(l.u + l.c, r.u + r.c), 0.f);
+        am = fminf(fminf(l.u - l.c, r.u - r.c), 0.f);
+        inv = frcp(ap - am);
+    } else {
+        auto side = [&](float hraw, const F3 &s) -> FaceSide {
+            const float h = fmaxf(hraw, 0.f), h2 = h * h, h4 = h2 * h2;
+            const bool deep = h >= thr;
+            // eq. (14): u = m * sqrt(2) h / sqrt(h^4 + max(h^4, eps))
+            const float f = deep ? frcp(h) : 1.41421356237f * h * frsq(h4 + fmaxf(h4, eps));
+            const float u = f * s.n, v = f * s.t, n = deep ? s.n : h * u, t = deep ? s.t : h * v;
+            const float e = h > 0.f ? s.e : -Df;
+            return {u, v, n, t, fsqrt(g * h), fmaf(hg * e, fmaf(2.f, Df, e), n * u)};
+        };
+        l = side(hL, L);
+        r = side(hR, R);
+        ap = fmaxf(fmaxf(l.u + l.c, r.u + r.c), 0.f);
+        am = fminf(fminf(l.u - l.c, r.u - r.c), 0.f);
+        dry = ap - am <= 1e-10f;
+        inv = frcp(dry ? 1.f : ap - am);
+    }
+    const float w = ap * inv, k = w * am, dn = l.n - r.n, tR = r.n * r.v;
+    H0 = fmaf(k, R.e - L.e, fmaf(w, dn, r.n));
+    H1 = fmaf(-k, dn, fmaf(w, l.F - r.F, r.F));
+    H2 = fmaf(-k, l.t - r.t, fmaf(w, fmaf(l.n, l.v, -tR), tR));
+    if (!wet) {
+        H0 = dry ? 0.f : H0;
+        H1 = dry ? -hg * Df * Df : H1;
+        H2 = dry ? 0.f : H2;
+    }
 }
 
 // Row/column system coefficients of eq. 23 for one cell, from the cell's

@@ -1,4 +1,4 @@
-"""Strip heights the library picks by itself (1, 2, 4 or 8 rows by the number
+"""Strip heights the library picks by itself (1, 2 or 8 rows by the number
 of waves a grid gives) against heights the caller sets: the same bits, alone
 and in a batch, for every kind of boundary and both friction laws (whose
 roundings must not depend on how far the row loop is unrolled)."""
@@ -26,14 +26,14 @@ def _same(a, b, what):
         assert np.isfinite(x).all() and np.array_equal(x, y), what
 
 
-# strips of 62 columns: waves at 1 row = ceil(nx / 62) * ny; 3200 is the limit
+# strips of 62 columns: ceil(nx / 62) * ceil(ny / rows) waves; 1 row up to 4096, 2 up to 72000
 @pytest.mark.parametrize("nx,ny,params", [
     (62, 9, dict(friction=2, friction_coef=0.03)),     # 1 row, one whole strip
     (63, 17, dict(friction=1, friction_coef=0.01)),    # 1 row, a strip of one column
-    (310, 640, dict()),                                # 3200 waves: the last of 1 row
-    (310, 643, dict(friction=2, friction_coef=0.03)),  # 2 rows, an odd last strip
-    (992, 417, dict(friction=1, friction_coef=0.01)),  # 4 rows, a last strip of one row
-    (1490, 1101, dict(n_corr=1)),                      # 8 rows
+    (310, 819, dict()),                                # 4095 waves: the last of 1 row
+    (310, 821, dict(friction=2, friction_coef=0.03)),  # 2 rows, an odd last strip
+    (992, 417, dict(friction=1, friction_coef=0.01)),  # 2 rows, a last strip of one row
+    (3100, 2883, dict(n_corr=1)),                      # 8 rows
 ])
 def test_own_heights_equal_set_heights(nx, ny, params):
     from paper_1611_05984_amd import wavestep as ws
