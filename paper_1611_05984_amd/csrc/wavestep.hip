@@ -1003,22 +1003,25 @@ static int short_rows(int nx, int ny) { return rows_for(strip_waves(nx, ny, 1), 
 
 // The workgroup shape follows the kernel: the corrector runs one-wave
 // workgroups, the predictors SWG strips a workgroup.
-static void launch_stencil(const ws_domain *d, int sy, hipStream_t st, const StencilArgs &sa) {
+static void launch_stencil(const ws_domain *d, int sy, hipStream_t st, const StencilArgs &sa,
+                           const GhostJob &job = GhostJob{0, nullptr, 0.0}) {
     const bool solo = sa.kind == 2;
     const dim3 grid = strips_for(d, sy, solo);
-    const dim3 g1(grid.x * grid.y);  // 1-D grid in XCD-aware tile order
+    const dim3 g1(grid.x * grid.y + (solo ? 0 : job.blocks));  // 1-D grid in XCD-aware tile order
     const int gx = (int)grid.x;
-#define L3(KERN) hipLaunchKernelGGL(KERN, g1, dim3(solo ? 64 : 64 * SWG), 0, st, sa, gx)
+#define LC(KERN) hipLaunchKernelGGL(KERN, g1, dim3(64), 0, st, sa, gx)
+#define LP(KERN) hipLaunchKernelGGL(KERN, g1, dim3(64 * SWG), 0, st, sa, gx, job)
     if (d->g.model == WS_NLSW) {
-        if (sa.kind == 2) SY_SWITCH(k_nlsw_c, sy, L3);
-        else if (sa.kind == 1) SY_SWITCH(k_nlsw_p, sy, L3);
-        else SY_SWITCH(k_nlsw_e, sy, L3);
+        if (sa.kind == 2) SY_SWITCH(k_nlsw_c, sy, LC);
+        else if (sa.kind == 1) SY_SWITCH(k_nlsw_p, sy, LP);
+        else SY_SWITCH(k_nlsw_e, sy, LP);
     } else {
-        if (sa.kind == 2) SY_SWITCH(k_stencil_c, sy, L3);
-        else if (sa.kind == 1) SY_SWITCH(k_stencil_p, sy, L3);
-        else SY_SWITCH(k_stencil_e, sy, L3);
+        if (sa.kind == 2) SY_SWITCH(k_stencil_c, sy, LC);
+        else if (sa.kind == 1) SY_SWITCH(k_stencil_p, sy, LP);
+        else SY_SWITCH(k_stencil_e, sy, LP);
     }
-#undef L3
+#undef LC
+#undef LP
 }
 // Equations per thread for systems of up to nred unknowns: a power of two.
 static int pcr_epl(int pnt, int nred) {
@@ -1263,11 +1266,11 @@ static void launch_solves(ws_domain *d, const SolveArgs &so, hipStream_t st) {
     }
 }
 
-static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st) {
+static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st, const GhostJob &job) {
     {
         ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
         const int rows = height(sa.kind == 2 && d->syc ? d->syc : d->sy, d->rows_by, short_rows(d->g.nx, d->g.ny));
-        launch_stencil(d, rows, st, sa);
+        launch_stencil(d, rows, st, sa, job);
     }
     launch_solves(d, so, st);
     HIPCHK(hipGetLastError());
@@ -1287,22 +1290,33 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
     const bool conv = d->tol_w > 0.0;
     const bool sponges = has_sponges(d);
     unsigned *dres = reinterpret_cast<unsigned *>(reinterpret_cast<char *>(d->health) + 128);
+    // the two ghost buffers change roles from step to step; a batch's tables
+    // hold them by name, so they leave as they came
+    struct Ghosts {
+        ws_domain *d;
+        float *g0, *g1;
+        ~Ghosts() { d->ghost[0] = g0, d->ghost[1] = g1; }
+    } ghosts{d, d->ghost[0], d->ghost[1]};
     for (int64_t n = 0; n < nsteps; ++n) {
         const int64_t s = d->step + 1;
         const bool euler = s <= 2;
         int K = euler ? 0 : d->g.n_corr;
         const double t0 = d->t, t1 = d->t + d->g.dt;
+        GhostJob job{0, nullptr, 0.0};
         if (makers) {
-            const int n = 8 * d->gl * GHL;
-            hipLaunchKernelGGL(k_ghosts, dim3((n + 255) / 256), dim3(256), 0, st, m, d->ghost[0], t0);
-            hipLaunchKernelGGL(k_ghosts, dim3((n + 255) / 256), dim3(256), 0, st, m, d->ghost[1], t1);
+            // the makers at t^n: evaluated for the call's first step, then the
+            // step before's t^{n+1}; at t^{n+1}: by the predictor's launch
+            const int nb = (8 * d->gl * GHL + 255) / 256;
+            if (n == 0) hipLaunchKernelGGL(k_ghosts, dim3(nb), dim3(256), 0, st, m, d->ghost[0], t0);
+            else std::swap(d->ghost[0], d->ghost[1]);
+            job = GhostJob{(nb + 7) / 8 * 8, d->ghost[1], t1};
         }
         StencilArgs sa;
         SolveArgs so;
         for (int p = 0; p <= K; ++p) {
             // (with a tolerance the sponge is applied once the count is known)
             pass_args(d, m, euler, d->cur, (int)(s % 3), p, sa, so, !conv);
-            ws_status r = run_pass(d, sa, so, st);
+            ws_status r = run_pass(d, sa, so, st, job);
             if (r != WS_OK) return r;
             if (p == 0) d->fs_zero[(s + 2) % 3] = d->g.model == WS_NLSW;  // the slot this step's predictor wrote
             if (conv && p >= 1) {
@@ -1632,8 +1646,7 @@ static void batch_solves(ws_batch *b, hipStream_t st, int p) {
 static ws_status batch_step(ws_batch *b, hipStream_t st) {
     const int n = (int)b->order.size();
     if (b->total[3] > 0) {
-        hipLaunchKernelGGL(kb_ghosts, dim3(b->total[3]), dim3(256), 0, st, b->d_desc, b->d_state, b->d_pre[3], n, 0);
-        hipLaunchKernelGGL(kb_ghosts, dim3(b->total[3]), dim3(256), 0, st, b->d_desc, b->d_state, b->d_pre[3], n, 1);
+        hipLaunchKernelGGL(kb_ghosts, dim3(b->total[3], 2), dim3(256), 0, st, b->d_desc, b->d_state, b->d_pre[3], n);
     }
     for (int p = 0; p <= b->maxK; ++p) {
         // predictor pass: stencil_rows; corrector passes: their own height

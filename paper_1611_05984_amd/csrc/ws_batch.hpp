@@ -308,10 +308,10 @@ __global__ __launch_bounds__(64) void kb_lu2_solve(const BatchDesc *__restrict__
     lu2_solve_body(A, b - prefix[dm], threadIdx.x);
 }
 
-// Wave-maker ghosts of t^n (which = 0) and t^{n+1} (which = 1); 256 threads
-// per block, 8 gl GHL threads per domain with wave makers.
-__global__ void kb_ghosts(const BatchDesc *descs, const BatchState *states, const int *prefix, int ndom,
-                          int which) {
+// Wave-maker ghosts of t^n (blockIdx.y = 0) and t^{n+1} (1); 256 threads per
+// block, 8 gl GHL threads per domain with wave makers.
+__global__ void kb_ghosts(const BatchDesc *descs, const BatchState *states, const int *prefix, int ndom) {
+    const int which = blockIdx.y;
     const int b = blockIdx.x, dm = find_dom(prefix, ndom, b);
     const BatchDesc &D = descs[dm];
     if (!D.makers || paused(states[dm])) return;

@@ -130,3 +130,38 @@ def test_nlsw_passes_follow_model_changes(nx, ny, sponge):
                 assert np.abs(x - y).max() <= 1e-5 * A0 * (math.sqrt(9.81 * DEPTH) if k else 1.0), k
     B.detach(slot)
     B.close()
+
+
+@pytest.mark.parametrize("nx,ny,model", [(2, 2, 0), (17, 90, 0), (510, 3, 0), (300, 130, 1)])
+def test_wave_makers_in_one_call_and_in_many(nx, ny, model):
+    """A call of several steps evaluates the makers once a time level (in the
+    predictor's launch), a call of one step both levels, a batch both in a
+    launch of its own: the same bits, also where a call of each kind follows
+    the other and where a second domain of the batch has no maker."""
+    print("case: makers %dx%d model %d" % (nx, ny, model), flush=True)
+    from paper_1611_05984_amd import wavestep as ws
+
+    def make():
+        d = _pair(nx, ny, 0, None, model=model)[0]
+        d.set_boundary(ws.NORTH, ws.WAVES, 2, [0.01] * 3, [1.2, 0.8, 0.5], [1.7, 1.2, -0.4], [0.5, 2.0, 0.1])
+        return d
+    one, many, b = make(), make(), make()
+    B = ws.Batch(2)
+    still, _ = _pair(20, 20, None, 1, model=model)
+    B.attach(still)
+    slot = B.attach(b)
+    for n in (7, 4):
+        one.advance(n)
+        for _ in range(n):
+            many.advance(1)
+        B.advance(n)
+        B.sync()
+        for x, y, z in zip(one.state_numpy(), many.state_numpy(), b.state_numpy()):
+            assert np.isfinite(x).all() and np.array_equal(x, y) and np.array_equal(x, z), n
+        B.detach(slot)
+        b.advance(3)
+        one.advance(3)
+        many.advance(2)
+        many.advance(1)
+        slot = B.attach(b)
+    B.close()
