@@ -44,20 +44,23 @@ TUNING_CACHE = os.path.join(ROOT, "paper_1611_05984_amd", "tuning_cache.txt")
 #   corrector: reads eta, P, Q, depth, bases (3); writes eta, dU*, dV* -> 7 + 3 = 10
 #   reduce:    reads dU*, dV*, depth; writes, per 16-cell row segment and
 #              16-cell column segment, two reduced equations (4 words each;
-#              PCR and lane Thomas) or two right-hand sides (factored solve)
+#              lane Thomas) or two right-hand sides (factored solve)
 #                                                           -> 3 + 1 or 0.25
-#   reduced solve: PCR reads the equations, writes the solutions: 1 + 0.25;
-#              lane Thomas also writes and rereads its sweep values: 1 + 0.5 +
-#              0.5 + 0.25; the factored solves (one- or two-ended) read the
-#              right-hand sides and three factors, write the solutions:
-#              0.25 + 0.75 + 0.25
+#   reduced solve: the PCR strategies run all solves of a pass as one kernel (no
+#              reduce, no expand): it reads dU*, dV*, P^n, Q^n, and depth and
+#              eta in rows and in columns; writes P, Q    -> 8 + 2;
+#              lane Thomas reads the equations, writes and rereads its sweep
+#              values, writes the solutions: 1 + 0.5 + 0.5 + 0.25; the factored
+#              solves (one- or two-ended) read the right-hand sides and three
+#              factors, write the solutions: 0.25 + 0.75 + 0.25
 #   expand:    reads dU*, dV* (2), P^n, Q^n, eta, depth, end values;
 #              writes P, Q                                  -> 6.25 + 2
 def alg_words(solver):
-    reduce_w = 3.25 if solver in (2, 3) else 4.0
-    solve_w = {0: 1.25, 1: 2.25, 2: 1.25, 3: 1.25, 4: 1.25}[solver]
+    one = solver in (0, 4)
+    reduce_w = 0.0 if one else 3.25 if solver in (2, 3) else 4.0
+    solve_w = {0: 10.0, 1: 2.25, 2: 1.25, 3: 1.25, 4: 10.0}[solver]
     return {"k_stencil[predictor]": 23.0, "k_stencil[corrector]": 10.0,
-            "k_reduce": reduce_w, "reduced_solve": solve_w, "k_expand": 8.25}
+            "k_reduce": reduce_w, "reduced_solve": solve_w, "k_expand": 0.0 if one else 8.25}
 
 
 def parse():
@@ -301,7 +304,7 @@ def kernel_symbol(cls, tuning):
     rows, _, solver, crows = tuning
     return {"k_stencil[predictor]": "k_stencil_p<%d>" % rows,
             "k_stencil[corrector]": "k_stencil_c<%d>" % (crows or rows),
-            "reduced_solve": ("k_pcr", "k_thomas", "k_luw_solve", "k_lu2_solve", "k_pcrw")[solver]}.get(cls, cls)
+            "reduced_solve": ("k_solve", "k_thomas", "k_luw_solve", "k_lu2_solve", "k_solve")[solver]}.get(cls, cls)
 
 
 def main():

@@ -322,7 +322,7 @@ ws_status ws_corrector_stats(const ws_domain *d, int32_t *last, int64_t *total, 
  * fill the chip; ws_get_tuning then reports the nominal heights.  pcr_threads: threads
  * per reduced tridiagonal system in the partitioned solve (64, 128 or 256:
  * equations held per thread versus threads per barrier; no effect on grids
- * of up to 16384 x 2048 cells, where the PCR strategies run a pass's solves as
+ * of up to 16384 x 4096 cells, where the PCR strategies run a pass's solves as
  * one kernel).  solver: the
  * reduced systems by PCR (WS_SOLVE_PCR) or by the Thomas algorithm with one
  * lane per system (WS_SOLVE_THOMAS: linear work, no barriers, a dependent
@@ -334,15 +334,12 @@ ws_status ws_corrector_stats(const ws_domain *d, int32_t *last, int64_t *total, 
  * refactored automatically after ws_set_boundary, terrain edits and
  * ws_restore) or by such factors of a
  * two-ended elimination (WS_SOLVE_LU2: two lanes per system meeting in the
- * middle, half the dependent chain) or by PCR on a single wave per system
- * (WS_SOLVE_PCR_WAVE: each lane holds equations k = lane + 64 j; the levels
- * of stride below 64 exchange equations by lane shuffles, the longer ones
- * within a lane's registers; no LDS array and no barrier; reduced systems of
- * up to 512 unknowns, i.e. grids up to 4096 cells in a direction:
- * ws_set_tuning returns WS_EINVAL for longer ones, and a batch whose largest
- * system is longer runs the workgroup PCR instead, which gives the same
- * bits).  The autotuners time each strategy together with the reduction it
- * needs (the factored solves' reduction writes right-hand sides only).
+ * middle, half the dependent chain) or by the wave form of PCR
+ * (WS_SOLVE_PCR_WAVE: reduced systems of up to 512 unknowns, i.e. grids up to
+ * 4096 cells in a direction, which the one kernel takes: the same as
+ * WS_SOLVE_PCR; ws_set_tuning returns WS_EINVAL for longer ones, and the
+ * longer domains of a batch run the workgroup PCR).  The autotuners time
+ * each strategy as all the solves of a pass.
  * Rows and threads do not change results (bitwise); THOMAS and LU give
  * the same bits, and so do PCR and PCR_WAVE; PCR, LU and LU2 round the
  * reduced solve differently. */

@@ -1035,24 +1035,17 @@ static int pcr_epl(int pnt, int nred) {
 template <int PNT, int EPL> struct PcrShape {
     static constexpr int threads = PNT, epl = EPL;
 };
+// The one-kernel solve takes every grid of up to 4096 rows and 16384 columns
+// of cells, so a system solved here has more than 512 and at most 2048 unknowns.
 template <class Go> static void pcr_dispatch(int pnt, int epl, Go go) {
     if (pnt == 64) {
-        if (epl <= 1) go(PcrShape<64, 1>());
-        else if (epl <= 2) go(PcrShape<64, 2>());
-        else if (epl <= 4) go(PcrShape<64, 4>());
-        else if (epl <= 8) go(PcrShape<64, 8>());
-        else if (epl <= 16) go(PcrShape<64, 16>());
+        if (epl <= 16) go(PcrShape<64, 16>());
         else go(PcrShape<64, 32>());
     } else if (pnt == 256) {
-        if (epl <= 1) go(PcrShape<256, 1>());
-        else if (epl <= 2) go(PcrShape<256, 2>());
-        else if (epl <= 4) go(PcrShape<256, 4>());
+        if (epl <= 4) go(PcrShape<256, 4>());
         else go(PcrShape<256, 8>());
     } else {
-        if (epl <= 1) go(PcrShape<128, 1>());
-        else if (epl <= 2) go(PcrShape<128, 2>());
-        else if (epl <= 4) go(PcrShape<128, 4>());
-        else if (epl <= 8) go(PcrShape<128, 8>());
+        if (epl <= 8) go(PcrShape<128, 8>());
         else go(PcrShape<128, 16>());
     }
 }
@@ -1065,23 +1058,9 @@ static void launch_pcr(int pnt, int nred, int nsys, hipStream_t st, const SolveA
     });
 }
 
-// The wave form of PCR (one wave per system, lane shuffles): equations per
-// lane the next power of two of nred / 64; systems of up to 512 unknowns.
-static bool pcrw_fits(int nred) { return nred <= 64 * PCRW_EPL_MAX; }
-static void launch_pcrw(int nred, int nsys, hipStream_t st, const SolveArgs &so) {
-    if (nred <= 64) hipLaunchKernelGGL(k_pcrw<1>, dim3(nsys), dim3(64), 0, st, so);
-    else if (nred <= 128) hipLaunchKernelGGL(k_pcrw<2>, dim3(nsys), dim3(64), 0, st, so);
-    else if (nred <= 256) hipLaunchKernelGGL(k_pcrw<4>, dim3(nsys), dim3(64), 0, st, so);
-    else hipLaunchKernelGGL(k_pcrw<8>, dim3(nsys), dim3(64), 0, st, so);
-}
-
-static void launch_pcrw_batch(int nred, dim3 pg, hipStream_t st, const BatchDesc *desc, const BatchState *state,
-                              const int *pre, int n, int p) {
-    if (nred <= 64) hipLaunchKernelGGL(kb_pcrw<1>, pg, dim3(64), 0, st, desc, state, pre, n, p);
-    else if (nred <= 128) hipLaunchKernelGGL(kb_pcrw<2>, pg, dim3(64), 0, st, desc, state, pre, n, p);
-    else if (nred <= 256) hipLaunchKernelGGL(kb_pcrw<4>, pg, dim3(64), 0, st, desc, state, pre, n, p);
-    else hipLaunchKernelGGL(kb_pcrw<8>, pg, dim3(64), 0, st, desc, state, pre, n, p);
-}
+// Grids whose strategy may be set to the wave form of PCR: reduced systems of
+// up to 512 unknowns, all solved by the one-kernel path.
+static bool pcrw_fits(int nred) { return nred <= 512; }
 
 static bool has_side(const ws_domain *d, int type) {
     for (int q = 0; q < 4; ++q)
@@ -1236,11 +1215,8 @@ static void launch_reduced(const ws_domain *d, hipStream_t st, const SolveArgs &
     } else if (d->solver == WS_SOLVE_THOMAS) {
         const int waves = (d->g.ny + 63) / 64 + (d->g.nx + 63) / 64;
         hipLaunchKernelGGL(k_thomas, dim3(waves), dim3(64), 0, st, so);
-    } else if (d->solver == WS_SOLVE_PCR_WAVE) {
-        launch_pcrw(nred_of(d), d->g.ny + d->g.nx, st, so);
     } else {
-        const int nred = d->nu > d->nv ? d->nu : d->nv;
-        launch_pcr(d->pnt, nred, d->g.ny + d->g.nx, st, so);
+        launch_pcr(d->pnt, nred_of(d), d->g.ny + d->g.nx, st, so);
     }
 }
 
@@ -1631,9 +1607,7 @@ static void batch_solves(ws_batch *b, hipStream_t st, int p) {
             hipLaunchKernelGGL(kb_lu_solve, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
     else if (b->solver == WS_SOLVE_THOMAS)
         hipLaunchKernelGGL(kb_thomas, pg, dim3(64), 0, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-    else if (b->solver == WS_SOLVE_PCR_WAVE && pcrw_fits(b->nred))  // (longer: the workgroup PCR, same bits)
-        launch_pcrw_batch(b->nred, pg, st, b->d_desc, b->d_state, b->d_pre[2], n, p);
-    else
+    else  // (also a batch set to the wave form: these systems are too long for it)
         pcr_dispatch(b->pnt, pcr_epl(b->pnt, b->nred), [&](auto shape) {
             using S = decltype(shape);
             hipLaunchKernelGGL((kb_pcr<S::threads, S::epl>), pg, dim3(S::threads), shm, st, b->d_desc,
@@ -2009,7 +1983,6 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
         time_solves(WS_SOLVE_PCR, PCR_NT);  // the thread counts and the wave form are the same kernel
     } else {
         for (int c : {64, 128, 256}) time_solves(WS_SOLVE_PCR, c);
-        if (pcrw_fits(nred_of(d))) time_solves(WS_SOLVE_PCR_WAVE, keep_pnt);  // (same bits as the above)
     }
     if (d->g.model != WS_NLSW)
         for (int sv : {WS_SOLVE_THOMAS, WS_SOLVE_LU, WS_SOLVE_LU2}) time_solves(sv, keep_pnt);
@@ -2130,7 +2103,6 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
             if ((r = time_solves(WS_SOLVE_PCR, c)) != WS_OK) return r;
             if (b->total[1] == 0) break;  // every domain on the one-kernel path: no thread counts
         }
-        if (b->total[1] > 0 && pcrw_fits(b->nred) && (r = time_solves(WS_SOLVE_PCR_WAVE, pnt0)) != WS_OK) return r;
         for (int sv : {WS_SOLVE_THOMAS, WS_SOLVE_LU, WS_SOLVE_LU2})
             if ((r = time_solves(sv, pnt0)) != WS_OK) return r;
     }

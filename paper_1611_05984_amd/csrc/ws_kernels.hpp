@@ -1,10 +1,13 @@
 // ws_kernels.hpp -- the gfx950 kernels of one predictor/corrector pass.
 //
-// A pass is the stencil and one launch of solves (ws_solve.hpp) where a
-// workgroup can hold the grid's columns, else four launches:
+// A dispersive pass is the stencil and one launch of solves (ws_solve.hpp)
+// where a workgroup can hold the grid's columns, else, and with the strategies
+// other than PCR, four launches (stencil, reduce, reduced, expand); an NLSW
+// pass is one launch, k_nlsw_{e,p,c}: its systems are identities, so the
+// stencil writes the discharges.
 //   k_stencil_{e,p,c}  (Euler predictor, AB3 predictor, AM4 corrector)
 //              column-streaming: one wave owns a strip of 64 columns (62 of
-//              them output) and walks 8-64 rows (tuned) with a sliding
+//              them output) and walks 1-64 rows (by rule or tuned) with a sliding
 //              register window;
 //              x-neighbours come from DPP lane shifts, so every face is
 //              reconstructed and fluxed once and no LDS or barrier is used.
@@ -20,7 +23,8 @@
 //              method); writes two reduced equations per segment (the
 //              eliminated interiors stay in LDS: the expansion redoes them).
 //   reduced    the reduced tridiagonal systems, by one of four strategies:
-//              k_pcr (parallel cyclic reduction, a workgroup per system),
+//              k_pcr (parallel cyclic reduction, a workgroup per system;
+//              for grids past the one-kernel solve's range),
 //              k_thomas (a lane per system), the factored sweeps with static
 //              factors (k_luw_solve: a workgroup per 64 systems held in
 //              registers; k_lu_solve: a lane per system) and the two-ended
@@ -29,7 +33,8 @@
 //              sides included) and back substitution from its solved end
 //              values, P = P^n + dP, Q = Q^n + dQ, shoreline fix (and the
 //              sponge after the last pass).
-// k_ghosts precomputes the wave-maker ghost values of one time level.
+// k_ghosts evaluates the wave makers at one time level, for the first step of
+// a call; later levels are evaluated within the predictor's launch.
 #pragma once
 #include "ws_device.hpp"
 
@@ -1198,8 +1203,7 @@ __global__ __launch_bounds__(64) void k_lu2_solve(SolveArgs A) { lu2_solve_body(
 // is sized for the actual systems.
 constexpr int PCR_NT = 128;  // default
 // One PCR level for equation e with its neighbours m (stride below) and p
-// (stride above), identity rows standing in past the system's ends: both
-// PCR forms call it, so they give the same bits.
+// (stride above), identity rows standing in past the system's ends.
 __device__ __forceinline__ float4 pcr_combine(float4 e, float4 m, float4 p) {
     const float al = -e.x * frcp(m.y), ga = -e.z * frcp(p.y);
     return make_float4(al * m.x, e.y + al * m.z + ga * p.x, ga * p.z, e.w + al * m.w + ga * p.w);
@@ -1237,94 +1241,6 @@ __device__ __forceinline__ void pcr_solve(int N, const float4 *src, float *dst, 
 #pragma unroll
     for (int j = 0; j < PCR_EPL; ++j)
         if (j < nmine) dst[tid + j * PNT] = eq[j].w / eq[j].y;
-}
-
-// PCR of one reduced system on a single wave, with no LDS array and no
-// barrier: equation k = lane + 64 j sits in register j of its lane.  At a
-// level of stride st < 64 the neighbours k - st and k + st are in lane
-// (lane -+ st) mod 64, register j or the next one out, and come by lane
-// shuffles (ds_bpermute); at st >= 64 they are the lane's own registers
-// j -+ st / 64.  The levels are unrolled, so every register index is a
-// compile-time constant.  Systems of up to 64 EPL unknowns.
-__device__ __forceinline__ float4 shfl4(float4 v, int src) {
-    return make_float4(__shfl(v.x, src), __shfl(v.y, src), __shfl(v.z, src), __shfl(v.w, src));
-}
-// Component-wise choice between two equations (a select of values: a ?: on
-// the vectors themselves can become a select of addresses, which puts the
-// register arrays in scratch memory).
-__device__ __forceinline__ float4 sel4(bool c, float4 a, float4 b) {
-    return make_float4(c ? a.x : b.x, c ? a.y : b.y, c ? a.z : b.z, c ? a.w : b.w);
-}
-// One level (stride 2^LV) of the wave form, for every equation of the lane.
-// Below stride 64 every neighbour is fetched by shuffles before any equation
-// changes, so the update runs in place; from 64 on the neighbours are the
-// lane's own registers and the new equations go to a fresh array first.
-template <int EPL, int LV>
-__device__ __forceinline__ void pcrw_level(int N, int lane, float4 (&eq)[EPL]) {
-    constexpr int st = 1 << LV;
-    const float4 id = make_float4(0.f, 1.f, 0.f, 0.f);
-    if constexpr (st < 64) {
-        const int up = (lane + st) & 63, dn = (lane - st) & 63;
-        float4 su[EPL], sd[EPL];  // equation j of lane up, of lane dn
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            su[j] = shfl4(eq[j], up);
-            sd[j] = shfl4(eq[j], dn);
-        }
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            const int k = lane + 64 * j;
-            const float4 hi = sel4(lane + st < 64, su[j], j + 1 < EPL ? su[j + 1] : id);
-            const float4 lo = sel4(lane >= st, sd[j], j > 0 ? sd[j - 1] : id);
-            eq[j] = pcr_combine(eq[j], sel4(k - st >= 0, lo, id), sel4(k + st < N, hi, id));
-        }
-    } else {
-        constexpr int q = st / 64;
-        float4 nw[EPL];
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-            const int k = lane + 64 * j;
-            const float4 hi = j + q < EPL ? eq[j + q] : id, lo = j >= q ? eq[j - q] : id;
-            nw[j] = pcr_combine(eq[j], sel4(k - st >= 0, lo, id), sel4(k + st < N, hi, id));
-        }
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) eq[j] = nw[j];
-    }
-}
-template <int EPL, int LV>
-__device__ __forceinline__ void pcrw_levels(int N, int lane, float4 (&eq)[EPL]) {
-    if constexpr ((1 << LV) < 64 * EPL) {
-        if ((1 << LV) < N) {
-            pcrw_level<EPL, LV>(N, lane, eq);
-            pcrw_levels<EPL, LV + 1>(N, lane, eq);
-        }
-    }
-}
-template <int EPL>
-__device__ __forceinline__ void pcrw_solve(int N, const float4 *src, float *dst) {
-    const int lane = threadIdx.x & 63;
-    const float4 id = make_float4(0.f, 1.f, 0.f, 0.f);
-    float4 eq[EPL];
-#pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-        const int k = lane + 64 * j;
-        eq[j] = sel4(k < N, src[k < N ? k : 0], id);
-    }
-    pcrw_levels<EPL, 0>(N, lane, eq);
-#pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-        const int k = lane + 64 * j;
-        if (k < N) dst[k] = eq[j].w / eq[j].y;
-    }
-}
-constexpr int PCRW_EPL_MAX = 8;  // the wave form takes systems of up to 512 unknowns
-
-template <int EPL>
-__global__ __launch_bounds__(64) void k_pcrw(SolveArgs A) {
-    const Dom &d = A.d;
-    const int sys = blockIdx.x;
-    if (sys < d.ny) pcrw_solve<EPL>(d.nu, A.redx + (size_t)sys * d.nu, A.solx + (size_t)sys * d.nu);
-    else pcrw_solve<EPL>(d.nv, A.redy + (size_t)(sys - d.ny) * d.nv, A.soly + (size_t)(sys - d.ny) * d.nv);
 }
 
 // System sys: rows 0..ny-1 (x direction), then columns.

@@ -18,8 +18,8 @@
 // 16-byte accesses); column workgroups read C consecutive columns of each
 // row, C lanes a run, straight into the owning lanes' registers.
 // us a pass's solves, three kernels (reduction, best PCR, expansion) / one:
-// 128 x 64 cells 17.5 / 9.8, 1024 x 512 20 / 11.7, 1024 x 1024 25 / 17, 2048 x
-// 1500 58 / 39.  Bound by latency up to about a million cells (4 us of launch,
+// 128 x 64 cells 17.5 / 9.5, 1024 x 512 20 / 11.8, 1024 x 1024 25 / 15.3, 2048 x
+// 1500 58 / 38.  Bound by latency up to about a million cells (4 us of launch,
 // two trips to memory), above by the columns' 32-byte runs: a workgroup pulls
 // whole 128-byte lines through its CU's 64 bytes a clock.
 #pragma once
