@@ -300,6 +300,8 @@ def k_variants(args, torch, ws, wl):
 
 # kernel class (as the library's event profiler reports it) -> the symbol the
 # profiler's kernel trace shows for the tuned launch shape
+# (of a grid large enough for 8-row strips; a smaller one runs 1- or 2-row
+# kernels at a nominal 8, and k_solve_big from 1025 rows of cells on)
 def kernel_symbol(cls, tuning):
     rows, _, solver, crows = tuning
     return {"k_stencil[predictor]": "k_stencil_p<%d>" % rows,

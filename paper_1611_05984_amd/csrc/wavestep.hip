@@ -1282,6 +1282,7 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
         if (makers) {
             // the makers at t^n: evaluated for the call's first step, then the
             // step before's t^{n+1}; at t^{n+1}: by the predictor's launch
+            static_assert(64 * SWG == 256, "the predictor's workgroups take as many ghost threads as k_ghosts'");
             const int nb = (8 * d->gl * GHL + 255) / 256;
             if (n == 0) hipLaunchKernelGGL(k_ghosts, dim3(nb), dim3(256), 0, st, m, d->ghost[0], t0);
             else std::swap(d->ghost[0], d->ghost[1]);

@@ -30,7 +30,11 @@ namespace ws {
 constexpr int FM = 16;    // cells a lane owns
 constexpr int FMT = 32;   // the same in columns of more than FS_TALL cells
 constexpr int FMP = 20;   // LDS stride of a row segment (floats)
-constexpr int FS_TALL = 2048;  // 128 segments x 8 columns: a workgroup's 1024 lanes
+// 128 segments x 8 columns: a workgroup's 1024 lanes.  Taking the tall form
+// earlier costs a second launch and gains nothing: us at a line of 2048 / of
+// 1024 cells: 2048 x 2048 49.2 / 50.1, 2048 x 1500 37.9 / 39.8, 1024 x 1100
+// 18.2 / 29.3.
+constexpr int FS_TALL = 2048;
 __host__ __device__ constexpr int fs_m(int ny) { return ny > FS_TALL ? FMT : FM; }
 
 // Threads of a workgroup (T, whole waves): 8 columns a run, at least one
