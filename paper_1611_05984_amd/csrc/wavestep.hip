@@ -1907,7 +1907,9 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     // increments; it reads the state and the older history levels only.
     StencilArgs sp;
     SolveArgs sop;
-    pass_args(d, m, d->step + 1 <= 2, d->cur, (int)((d->step + 1) % 3), 0, sp, sop);
+    const int sm = (int)((d->step + 1) % 3);
+    pass_args(d, m, d->step + 1 <= 2, d->cur, sm, 0, sp, sop);
+    if (d->g.model == WS_BSNQ) d->fs_zero[(sm + 2) % 3] = false;  // the slot the trials leave F*, G* in
     if (d->g.model == WS_NLSW) sa.health = sp.health = (int *)d->scal;  // (its stencil reports the health)
     const int rows[6] = {8, 16, 24, 32, 48, 64};
     float t_rows[2][6];
