@@ -158,7 +158,10 @@ ws_status ws_domain_destroy(ws_domain *d);
 ws_status ws_domain_init_static(const ws_grid *g, const float *z_corners_dev, void *stream,
                                 ws_domain **out);
 
-/* Boundary condition of one side (WS_WEST..WS_NORTH).  Synchronous. */
+/* Boundary condition of one side (WS_WEST..WS_NORTH), from the next
+ * ws_advance or ws_batch_advance on: steps already queued keep the sponges
+ * they were queued with (a wave maker's components are replaced at once).
+ * Synchronous. */
 ws_status ws_set_boundary(ws_domain *d, int32_t side, const ws_boundary *b);
 
 /* Change parameters of a running domain (the paper's interactive changes of
@@ -195,7 +198,9 @@ ws_status ws_add_solitary(ws_domain *d, double H, double theta, double x0, doubl
                           void *stream);
 
 /* Advance nsteps full time steps (predictor + n_corr correctors each).
- * Asynchronous on `stream`. */
+ * Asynchronous on `stream`.  A call captured into a graph holds the
+ * parameters, boundaries and bathymetry of the capture: capture again after
+ * changing one. */
 ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream);
 
 /* Copy the state to device arrays (row pitch `pitch`): first field w

@@ -47,7 +47,8 @@ struct ws_domain {
     size_t bytes;
     float *D;                      // corner still-water depth
     float *Dnew;                   // k_cells' field (depths of the cells, sponge factors); a terrain edit
-                                   // builds the new corners here first and refills it
+                                   // builds the new corners here first
+    bool cells_stale;              // that field is not k_cells' of the present bathymetry and sponges
     float *st[3][3];               // state of the step and two estimates (eta, P, Q)
     float *rx, *ry;                // U*, V* increments / eliminated segments
     float *S[3];                   // corrector bases
@@ -389,10 +390,23 @@ __global__ void k_side_depth(Dom d, int side, double *out) {
 }
 
 static dim3 cells_grid(int nx, int ny) { return dim3((nx + 255) / 256, ny); }
-// To be called whenever the bathymetry, a sponge or the time step (which
-// partially reflective sponges scale with) changed.
 static void refresh_cells(const ws_domain *d, hipStream_t st) {
     hipLaunchKernelGGL(k_cells, cells_grid(d->g.nx + 1, d->g.ny + 1), dim3(256), 0, st, make_dom(d), d->Dnew);
+}
+// The cell field, where the bathymetry, a sponge or the time step (which
+// partially reflective sponges scale with) changed since: by the call that is
+// about to launch passes, on its stream.  The calls that change those only
+// mark the field: passes of earlier calls may still be reading it, on a
+// stream that the changing call does not know, and its old corners with it.
+static ws_status ensure_cells(ws_domain *d, hipStream_t st) {
+    if (!d->cells_stale) return WS_OK;
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (st) HIPCHK(hipStreamIsCapturing(st, &cs));
+    refresh_cells(d, st);
+    HIPCHK(hipGetLastError());
+    // a captured refresh has not run: the next call makes its own
+    d->cells_stale = cs != hipStreamCaptureStatusNone;
+    return WS_OK;
 }
 
 // Largest change between two iterates of the state over the interior cells:
@@ -701,9 +715,7 @@ extern "C" ws_status ws_set_boundary(ws_domain *d, int32_t side, const ws_bounda
     d->side_R[side] = R;
     d->side_depth[side] = dside;
     d->side_expo[side] = sponge_expo(d, side);
-    refresh_cells(d, 0);
-    HIPCHK(hipGetLastError());
-    HIPCHK(hipStreamSynchronize(0));
+    d->cells_stale = true;
     if (nc > 0 && !(dref > 0.0)) return fail(WS_EINVAL, "ws_set_boundary: no positive depth along the side");
     std::vector<double> tab((size_t)MAXC * TABW, 0.0);
     const double g = d->g.g;
@@ -761,8 +773,7 @@ extern "C" ws_status ws_update_grid(ws_domain *d, const ws_grid *g, void *stream
         d->step = 0;
         for (int q = 0; q < 4; ++q)
             if (d->side_type[q] == WS_BC_SPONGE) d->side_expo[q] = sponge_expo(d, q);
-        refresh_cells(d, (hipStream_t)stream);
-        HIPCHK(hipGetLastError());
+        d->cells_stale = true;
     }
     if (systems) d->lu_valid = false;
     batch_touch(d);
@@ -849,7 +860,7 @@ extern "C" ws_status ws_restore(ws_domain *d, const void *src_dev, size_t bytes,
     HIPCHK(hipMemcpyAsync(d->hist[0][0], p, 15 * fb, hipMemcpyDeviceToDevice, st));
     p += 15 * fb;
     HIPCHK(hipMemcpyAsync(d->D, p, cb, hipMemcpyDeviceToDevice, st));
-    refresh_cells(d, st);
+    d->cells_stale = true;
     HIPCHK(hipMemsetAsync(d->health, 0, sizeof(int), st));
     d->cur = 0;
     for (bool &z : d->fs_zero) z = false;
@@ -941,6 +952,7 @@ extern "C" ws_status ws_apply_edit(ws_domain *d, int32_t kind, double x0, double
         return WS_OK;
     }
     if (kind != WS_EDIT_RAISE_TERRAIN) return fail(WS_EINVAL, "ws_apply_edit: bad kind %d", kind);
+    d->cells_stale = true;  // (also where the edit is rejected)
     hipLaunchKernelGGL(k_edit_terrain, cells_grid(d->g.nx + 1, d->g.ny + 1), dim3(256), 0, st, m, d->D,
                        d->Dnew, x0, y0, amp, sigma);
     Dom mn = m;
@@ -951,18 +963,13 @@ extern "C" ws_status ws_apply_edit(ws_domain *d, int32_t kind, double x0, double
     int flag = 0;
     HIPCHK(hipMemcpyAsync(&flag, d->scal, sizeof(int), hipMemcpyDeviceToHost, st));
     HIPCHK(hipStreamSynchronize(st));
-    if (flag) {
-        refresh_cells(d, st);
-        HIPCHK(hipGetLastError());
-        return fail(WS_ENOTDD, "ws_apply_edit: terrain edit rejected (eq. 23 would lose diagonal dominance)");
-    }
+    if (flag) return fail(WS_ENOTDD, "ws_apply_edit: terrain edit rejected (eq. 23 would lose diagonal dominance)");
     std::swap(d->D, d->Dnew);
     d->lu_valid = false;
     batch_touch(d);
     m = make_dom(d);
     hipLaunchKernelGGL(k_edit_velocity, cells_grid(d->g.nx, d->g.ny), dim3(256), 0, st, m, d->Dnew, e, p, q);
     hipLaunchKernelGGL(k_shore_fix, cells_grid(d->g.nx, d->g.ny), dim3(256), 0, st, m, e, p, q);
-    refresh_cells(d, st);
     HIPCHK(hipGetLastError());
     return WS_OK;
 }
@@ -1258,7 +1265,8 @@ extern "C" ws_status ws_advance(ws_domain *d, int64_t nsteps, void *stream) {
     if (d->batch) return fail(WS_EBUSY, "ws_advance: domain is attached to a batch (use ws_batch_advance)");
     hipStream_t st = (hipStream_t)stream;
     if (nsteps > 0) {
-        ws_status r = ensure_factors(d, st);
+        ws_status r = ensure_cells(d, st);
+        if (r == WS_OK) r = ensure_factors(d, st);
         if (r != WS_OK) return r;
     }
     const Dom m = make_dom(d);
@@ -1750,7 +1758,8 @@ extern "C" ws_status ws_batch_advance(ws_batch *b, int64_t nsteps, void *stream)
     }
     if (b->order.empty() || nsteps == 0) return WS_OK;
     for (int sl : b->order) {
-        ws_status r = ensure_factors(b->slots[sl], st);
+        ws_status r = ensure_cells(b->slots[sl], st);
+        if (r == WS_OK) r = ensure_factors(b->slots[sl], st);
         if (r != WS_OK) return r;
     }
     b->last = st;
@@ -1876,6 +1885,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
         return r;
     }
     hipStream_t st = (hipStream_t)stream;
+    if (ensure_cells(d, st) != WS_OK) return WS_EHIP;
     // a corrector pass reads the current state and the corrector bases and
     // writes only the scratch estimate, the U*, V* increments and the solver
     // scratch: the state and history are untouched
@@ -2044,6 +2054,8 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
         if ((r = batch_upload(b)) != WS_OK) return r;
         const int n = (int)b->order.size();
         if (n == 0) break;
+        for (int sl : b->order)
+            if ((r = ensure_cells(b->slots[sl], st)) != WS_OK) return r;
         // pass 0: each domain's next predictor (it rewrites only what that
         // step's predictor rewrites first); pass 1: a corrector (scratch only)
         float ms[2];

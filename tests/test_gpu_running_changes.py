@@ -60,3 +60,105 @@ def test_tuning_leaves_later_model_changes_alone(nx, ny, before):
         runs.append((d, r))
     _same(runs[0][0], runs[1][0], "steps after the model change")
     _same(runs[0][1], runs[1][1], "steps after a restore")
+
+
+@pytest.mark.parametrize("model", [0, 1])
+@pytest.mark.parametrize("change", ["sponge", "terrain", "dt"])
+def test_changes_leave_queued_steps_alone(model, change):
+    """Boundary, terrain and time-step changes right after steps were queued
+    on a stream that the null stream does not wait for, against the same with
+    the GPU waited for before every call."""
+    import torch
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: %s behind queued steps, model %d" % (change, model), flush=True)
+    st = torch.cuda.Stream()
+    runs = []
+    for wait in (True, False):
+        d = _domain(1024, 700, model=model)
+        d.set_boundary(ws.NORTH, ws.SPONGE, 30, sponge_reflect=0.3)
+        torch.cuda.synchronize()
+        pause = torch.cuda.synchronize if wait else (lambda: None)
+        for k in range(3):
+            d.advance(60, stream=st)
+            pause()
+            if change == "terrain":
+                assert d.apply_edit(ws.EDIT_TERRAIN, 15.0 + 5 * k, 12.0, 0.05, 2.0, stream=st) == 0
+                pause()
+            if change == "dt":
+                d.update(dt=d.g.dt * 0.9)       # on the current stream, not the steps'
+                pause()
+            else:
+                d.set_boundary(ws.EAST, ws.SPONGE, 40 + 100 * k)
+                d.set_boundary(ws.SOUTH, (ws.SPONGE, ws.SOLID)[k % 2], 25)
+                pause()
+        d.advance(4, stream=st)
+        torch.cuda.synchronize()
+        assert d.query()[2] == 0
+        runs.append(d)
+    _same(runs[0], runs[1], change)
+
+
+@pytest.mark.parametrize("nx,ny,model", [(90, 50, 0), (600, 530, 0), (40, 2100, 0), (90, 50, 1)])
+def test_boundary_change_on_a_running_domain(nx, ny, model):
+    """Steps, new sponges, more steps; against a fresh domain that had those
+    sponges from the start and took the state over; alone and in a batch."""
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: sponges set on a running %dx%d model %d" % (nx, ny, model), flush=True)
+
+    def sponges(d):
+        d.set_boundary(ws.EAST, ws.SPONGE, 12)
+        d.set_boundary(ws.SOUTH, ws.SPONGE, 9, sponge_reflect=0.2)
+        d.set_boundary(ws.WEST, ws.SOLID)
+
+    a, f, b = (_domain(nx, ny, model=model) for _ in range(3))
+    sponges(f)
+    B = ws.Batch(1)
+    B.attach(b)
+    for d in (a, b):
+        d.set_boundary(ws.WEST, ws.SPONGE, 7)
+    a.advance(5)
+    B.advance(5)
+    B.sync()
+    f.restore(a.snapshot())
+    sponges(a)
+    sponges(b)
+    a.advance(4)
+    f.advance(4)
+    B.advance(4)
+    B.sync()
+    _same(a, f, "fresh domain")
+    _same(a, b, "batch")
+    B.close()
+
+
+@pytest.mark.parametrize("model", [0, 1])
+def test_boundary_change_before_a_captured_call(model):
+    """A boundary change, a capture of the next steps, the same steps eagerly
+    before the capture ever ran, then the capture replayed between eager
+    steps: three steps each time, after which all buffers have their roles
+    again."""
+    import torch
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: capture behind a boundary change, model %d" % model, flush=True)
+    a, r = _domain(200, 90, model=model), _domain(200, 90, model=model)
+    for d in (a, r):
+        d.advance(3)
+        d.set_boundary(ws.EAST, ws.SPONGE, 30)
+    torch.cuda.synchronize()
+    st = torch.cuda.Stream()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        a.advance(3, stream=st)
+    a.advance(3)
+    r.advance(3)
+    torch.cuda.synchronize()
+    _same(a, r, "eager steps before the first replay")
+    for k in range(3):
+        g.replay()
+        torch.cuda.synchronize()
+        r.advance(3)
+        _same(a, r, "replay %d" % k)
+        a.advance(3)
+        r.advance(3)
+        torch.cuda.synchronize()
+        _same(a, r, "eager steps after replay %d" % k)
