@@ -73,8 +73,8 @@ constexpr size_t fs_lds(int T) { return (size_t)T * FMP * sizeof(float); }
 // f.y x_last; l: l.x x_first + l.y x_last + l.z x_{+1} = l.w.  The line's
 // ends fold as in seg_coefs (glo, ghi: the maker's discharge change, 0 behind
 // a wall), by selects: a branch had the compiler copy all the arrays.  Cells
-// past the end need not be identity rows: no cell of the line refers to
-// them.  Coefficients and forward elimination go cell by cell, with a
+// past the end need not be identity rows, as no cell of the line refers to
+// them, but finite ones: the callers give them the ghost's depth.  Coefficients and forward elimination go cell by cell, with a
 // scheduling fence every few, so that the depths die as the rows are born.
 template <int M>
 __device__ __forceinline__ void fs_eliminate(TriK tk, int i0, int n, bool lo_wall, bool hi_wall, float glo, float ghi,
@@ -247,13 +247,15 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
         r[k + 2] = v.z;
         r[k + 3] = v.w;
     }
-    {   // the ghost past the row's last cell: mirrored, or held behind a maker
+    {   // the ghost past the row's last cell: mirrored, or held behind a maker; and the
+        // same for the cells after it: the field holds other data there (old
+        // corners, after a terrain edit), whose pivots can vanish
         const int kl = d.nx - 1 - i0;
         const bool wall = is_wall(d, 1);
 #pragma unroll
         for (int k = 0; k < FM; ++k) {
             const float gd = wall ? dep[k + 1] : dhi;
-            dep[k + 2] = k == kl ? gd : dep[k + 2];
+            dep[k + 2] = k < kl ? dep[k + 2] : gd;
         }
     }
     __syncthreads();

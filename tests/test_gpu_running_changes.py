@@ -162,3 +162,40 @@ def test_boundary_change_before_a_captured_call(model):
         r.advance(3)
         torch.cuda.synchronize()
         _same(a, r, "eager steps after replay %d" % k)
+
+
+@pytest.mark.parametrize("ny,batched", [(20, False), (20, True), (2060, False)])
+def test_terrain_edit_leaves_nothing_beyond_the_rows(ny, batched):
+    """The field of cell depths is built in the memory of the corners before
+    the last terrain edit, and its rows are padded with them.  Corners chosen
+    so that four of them in a row (0, 1, 42, 6/7 m deep, B = 1/6, dx = 1 m),
+    taken for cell depths, have a pivot of exactly zero; every cell is 21 m
+    deep.  The solves must not see them: the Thomas path's result, within the
+    bound the strategies are held to."""
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: pads behind rows of 17 cells, ny %d" % ny, flush=True)
+    nx = 17
+    s = np.tile([0.0, 0.0, 0.0, 0.0, 1.0, 42.0, 6.0 / 7.0, 0.0], 3)[:nx + 1] - 21.0
+    z = -(21.0 - np.where(np.arange(ny + 1)[:, None] % 2, -1.0, 1.0) * s[None, :])
+
+    def make():
+        d = ws.Domain(nx, ny, 1.0, 1.0, 0.005, z, Bcoef=1.0 / 6.0)
+        assert d.apply_edit(ws.EDIT_WATER, 8.0, 9.0, 0.05, 3.0) == 0
+        for _ in range(2):      # either of the two corner arrays may be the field's
+            assert d.apply_edit(ws.EDIT_TERRAIN, 3.0, 15.0, 1e-3, 1.0) == 0
+        return d
+
+    a, t = make(), make()
+    t.set_tuning(16, 128, ws.SOLVE_THOMAS)
+    t.advance(6)
+    if batched:
+        B = ws.Batch(1)
+        B.attach(a)
+        B.advance(6)
+        B.sync()
+        B.close()
+    else:
+        a.advance(6)
+    for x, y in zip(a.state_numpy(), t.state_numpy()):
+        assert np.isfinite(x).all() and np.abs(x - y).max() <= 1e-6 * max(1.0, np.abs(y).max())
+    assert a.query()[2] == 0
