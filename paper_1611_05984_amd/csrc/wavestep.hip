@@ -1086,7 +1086,11 @@ static bool fused(const ws_domain *d) {
 static void launch_solve(const ws_domain *d, hipStream_t st, const SolveArgs &so) {
     const int T = fs_threads(d->g.nx, d->g.ny);
     const dim3 grid(fs_row_groups(T, d->g.nx, d->g.ny) + fs_col_groups(T, d->g.nx, d->g.ny));
-    if (d->g.ny > FS_TALL) {
+    if (fs_narrow(d->g.nx, d->g.ny)) {
+        const int Tn = fs_narrow_threads(d->g.ny);
+        const dim3 gn(fs_row_groups(Tn, d->g.nx, d->g.ny) + fs_col_groups(Tn, d->g.nx, d->g.ny));
+        hipLaunchKernelGGL(k_solve_tall, gn, dim3(Tn), fs_lds(Tn), st, so);
+    } else if (d->g.ny > FS_TALL) {
         const int need = fs_segs(d->g.nx), Tr = need <= 256 ? 256 : (need + 63) / 64 * 64, R = fs_rows(Tr, d->g.nx);
         hipLaunchKernelGGL(k_solve_rows, dim3((d->g.ny + R - 1) / R), dim3(Tr), fs_lds(Tr), st, so);
         hipLaunchKernelGGL(k_solve_cols, dim3(fs_col_groups(T, d->g.nx, d->g.ny)), dim3(T), fs_lds(T), st, so);

@@ -47,13 +47,22 @@ inline int fs_threads(int nx, int ny) {
     const int need = 8 * fs_segs(ny, fs_m(ny)), m = need > fs_segs(nx) ? need : fs_segs(nx);
     return m <= 256 ? 256 : (m + 63) / 64 * 64;
 }
+// A tall grid of up to FS_NARROW columns of cells runs in one launch (k_solve_tall)
+// of 4 columns a run: at 8 it gives too few workgroups, and its rows, in a
+// launch of their own, are over in a moment.  us a step of the three kernels /
+// rows and columns apart / one launch: 48 x 3000 cells 94 / 118 / 90, 48 x 4096
+// 111 / 142 / 114, 256 x 2500 129 / 138 / 104, 512 x 3000 192 / 182 / 165; 700 x 2500
+// (rows and columns apart / one launch) 186 / 189.
+constexpr int FS_NARROW = 512;
+inline bool fs_narrow(int nx, int ny) { return ny > FS_TALL && nx <= FS_NARROW; }
+inline int fs_narrow_threads(int ny) { return (4 * fs_segs(ny, FMT) + 63) / 64 * 64; }
 inline bool fs_fits(int nx, int ny) { return ny <= 2 * FS_TALL && fs_segs(nx) <= 1024; }
-// Rows of a row workgroup, columns of a column workgroup (a power of two, at
-// most 64), workgroups of each (rows padded to the 8 XCDs).
+// Rows of a row workgroup, columns of a column workgroup (a power of two, 4 to
+// 64), workgroups of each (rows padded to the 8 XCDs).
 __host__ __device__ inline int fs_rows(int T, int nx) { return T / fs_segs(nx); }
 __host__ __device__ inline int fs_cols(int T, int ny, int M) {
     const int c = T / fs_segs(ny, M);
-    return c >= 64 ? 64 : c >= 32 ? 32 : c >= 16 ? 16 : 8;
+    return c >= 64 ? 64 : c >= 32 ? 32 : c >= 16 ? 16 : c >= 8 ? 8 : 4;
 }
 __host__ __device__ inline int fs_row_groups(int T, int nx, int ny) {
     const int r = fs_rows(T, nx);
@@ -429,7 +438,7 @@ __device__ __forceinline__ void solve_body(const SolveArgs &A, float *lds, int b
         const int g = xcd_order(b, nr);
         if (g * fs_rows(T, A.d.nx) < A.d.ny) solve_rows<EARLY>(A, lds, T, g);
     } else if (TALL && A.d.ny > FS_TALL) {
-        solve_cols<FMT, false>(A, lds, T, xcd_order(b - nr, nc));
+        solve_cols<FMT, EARLY>(A, lds, T, xcd_order(b - nr, nc));
     } else {
         solve_cols<FM, EARLY>(A, lds, T, xcd_order(b - nr, nc));
     }
@@ -447,8 +456,13 @@ __global__ __launch_bounds__(1024) void k_solve_big(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
     solve_body<false>(A, fs_buf, blockIdx.x);
 }
-// Columns of more than FS_TALL cells fill a CU's registers with one workgroup,
-// so the rows get a launch of their own, with small workgroups.
+__global__ __launch_bounds__(FS_EARLY) void k_solve_tall(SolveArgs A) {
+    extern __shared__ __align__(16) float fs_buf[];
+    solve_body<true, true>(A, fs_buf, blockIdx.x);
+}
+// Wider grids, at 8 columns a run: columns of more than FS_TALL cells fill a
+// CU's registers with one workgroup, so the rows get a launch of their own,
+// with small workgroups.
 __global__ __launch_bounds__(1024) void k_solve_rows(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
     solve_rows<false>(A, fs_buf, blockDim.x, xcd_order(blockIdx.x, gridDim.x));
