@@ -321,10 +321,11 @@ ws_status ws_corrector_stats(const ws_domain *d, int32_t *last, int64_t *total, 
  * and in the corrector passes too unless corrector_rows (same choices) is
  * set: the predictor moves twice the corrector's bytes and the corrector
  * is bound by instruction issue, so their best heights can differ; 0 =
- * stencil_rows for every pass.  Until a caller sets heights (ws_set_tuning,
- * ws_batch_set_tuning), and after an autotuner picked 8, the library runs
- * shorter strips (8 to 1 rows) where the grid or batch has too few waves to
- * fill the chip; ws_get_tuning then reports the nominal heights.  pcr_threads: threads
+ * stencil_rows for every pass.  8, the default, stands for the shortest
+ * strips that pay: 1 row on grids (batches: on all domains together) that
+ * give up to 4096 strips of one row, 2 rows up to 72000 strips of two (about
+ * 9 million cells), 8 rows beyond; the autotuners and ws_get_tuning return it
+ * as 8, and setting it again runs the same.  pcr_threads: threads
  * per reduced tridiagonal system in the partitioned solve (64, 128 or 256:
  * equations held per thread versus threads per barrier; no effect on grids
  * of up to 16384 x 4096 cells, where the PCR strategies run a pass's solves as
@@ -359,7 +360,7 @@ typedef struct {
 } ws_tuning;
 ws_status ws_get_tuning(const ws_domain *d, ws_tuning *out);
 ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t);
-/* Tuning of a batch (shared by its domains; nominal default 32 rows, 128 threads). */
+/* Tuning of a batch (shared by its domains; default 8 rows, 128 threads). */
 ws_status ws_batch_set_tuning(ws_batch *b, const ws_tuning *t);
 /* Autotuner: times every candidate launch shape on this domain's grid
  * (predictor- and corrector-pass stencils and the reduced solves, HIP events

@@ -80,7 +80,6 @@ struct ws_domain {
     int sy, pnt, solver;           // tuning: stencil rows per strip, PCR threads per system, reduced solver
     int syc;                       // stencil rows per strip in corrector passes (0: sy)
     bool fs_zero[3];               // history slots whose F*, G* are known to be zero (NLSW steps)
-    int rows_by;                   // who chose the heights above (ROWS_*)
     size_t fstride;                // bytes between consecutive fields
     StencilArgs *vsa;              // pass argument tables (device), batch use only
     SolveArgs *vso;
@@ -92,11 +91,10 @@ struct ws_domain {
     int static_dev;                // device whose static array holds the workspace (-1: the caller's)
 };
 
-// Heights nobody chose follow short_rows(); so does the autotuner's 8.
-enum { ROWS_NOBODY = 0, ROWS_CALLER = 1, ROWS_TUNER = 2 };
-static int height(int nominal, int by, int rule) {
-    return by == ROWS_NOBODY || (by == ROWS_TUNER && nominal == 8) ? rule : nominal;
-}
+// The shortest nominal height, and the default, stands for the rule's (rows_for):
+// 8 rows or fewer, whoever asks for it, so a choice that the autotuners or
+// ws_get_tuning return can be set again and runs what it ran.
+static int height(int nominal, int rule) { return nominal == SY ? rule : nominal; }
 
 static ws_status busy_check(const ws_domain *d, const char *who) {
     if (d->batch && d->stale) return fail(WS_EBUSY, "%s: domain advanced by its batch; call ws_batch_sync first", who);
@@ -981,8 +979,8 @@ static dim3 strips_for(const ws_domain *d, int sy, bool solo = false) {
     return dim3(solo ? ns : (ns + SWG - 1) / SWG, (d->g.ny + sy - 1) / sy);
 }
 
-// Strip height where the caller chose none (or the autotuner its shortest).
-// One wave walks a strip row by row after three warm-up rows; a shorter strip
+// Strip height where the shortest is asked for.
+// One wave walks a strip row by row after four warm-up rows; a shorter strip
 // repeats more warm-up rows, from cache, but starts more waves, and up to two
 // rows the loop is unrolled.  1 row while its waves fit the chip at once, 2 up
 // to about 9 million cells, beyond that 8: there the repeated rows go to
@@ -1256,7 +1254,7 @@ static void launch_solves(ws_domain *d, const SolveArgs &so, hipStream_t st) {
 static ws_status run_pass(ws_domain *d, const StencilArgs &sa, const SolveArgs &so, hipStream_t st, const GhostJob &job) {
     {
         ProfScope p(d, st, sa.kind == 2 ? WS_K_CORRECTOR : WS_K_PREDICTOR);
-        const int rows = height(sa.kind == 2 && d->syc ? d->syc : d->sy, d->rows_by, short_rows(d->g.nx, d->g.ny));
+        const int rows = height(sa.kind == 2 && d->syc ? d->syc : d->sy, short_rows(d->g.nx, d->g.ny));
         launch_stencil(d, rows, st, sa, job);
     }
     launch_solves(d, so, st);
@@ -1399,14 +1397,13 @@ struct ws_batch {
     hipGraphExec_t exec = nullptr;
     hipStream_t gstream = nullptr;
     hipStream_t last = nullptr;
-    int sy = SY, pnt = PCR_NT, solver = WS_SOLVE_PCR;  // tuning shared by all domains of the batch
+    int sy = SY, pnt = PCR_NT, solver = WS_SOLVE_PCR;   // tuning shared by all domains of the batch
     int syc = 0;                                        // corrector-pass stencil rows (0: sy)
-    int rows_by = ROWS_NOBODY;                          // who chose the heights
     int rp = SY, rc = SY;                               // heights the tables were built for
 };
 
-// Strip heights of the batch: the caller's or the autotuner's, else by the
-// rule of short_rows() on the waves of all its domains together.
+// Strip heights of the batch, the shortest by the rule of short_rows() on the
+// waves of all its domains together.
 static void batch_rows(ws_batch *b, const std::vector<int> &order) {
     long w1 = 0, w2 = 0;
     for (int sl : order) {
@@ -1415,8 +1412,8 @@ static void batch_rows(ws_batch *b, const std::vector<int> &order) {
         w2 += strip_waves(g.nx, g.ny, 2);
     }
     const int rule = rows_for(w1, w2);
-    b->rp = height(b->sy, b->rows_by, rule);
-    b->rc = height(b->syc ? b->syc : b->sy, b->rows_by, rule);
+    b->rp = height(b->sy, rule);
+    b->rc = height(b->syc ? b->syc : b->sy, rule);
 }
 
 static size_t batch_layout(int max, size_t *o_state, size_t *o_pre) {
@@ -1827,7 +1824,6 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
                     nred_of(d));
     d->sy = t->stencil_rows;
     d->syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
-    d->rows_by = ROWS_CALLER;
     d->pnt = t->pcr_threads;
     if (d->solver != t->solver) batch_touch(d);  // argument blocks carry the solve layout
     d->solver = t->solver;
@@ -1837,23 +1833,15 @@ extern "C" ws_status ws_set_tuning(ws_domain *d, const ws_tuning *t) {
 extern "C" ws_status ws_batch_set_tuning(ws_batch *b, const ws_tuning *t) {
     if (!b || !tuning_ok(t)) return fail(WS_EINVAL, "ws_batch_set_tuning: bad tuning");
     const int syc = t->corrector_rows == t->stencil_rows ? 0 : t->corrector_rows;
-    if (b->rows_by != ROWS_CALLER || b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
+    if (b->sy != t->stencil_rows || b->syc != syc || b->pnt != t->pcr_threads || b->solver != t->solver) {
         b->sy = t->stencil_rows;
         b->syc = syc;
         b->pnt = t->pcr_threads;
         b->solver = t->solver;
-        b->rows_by = ROWS_CALLER;
         b->dirty = true;
         b->total[0] = -1;  // launch shapes change: the captured step is rebuilt
     }
     return WS_OK;
-}
-
-// The autotuner's choice, applied: its shortest height may be shortened.
-static ws_status set_tuned(ws_domain *d, const ws_tuning *t) {
-    const ws_status r = ws_set_tuning(d, t);
-    if (r == WS_OK) d->rows_by = ROWS_TUNER;
-    return r;
 }
 
 static bool cache_lookup(const char *path, const ws_grid &g, ws_tuning *t) {
@@ -1884,7 +1872,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     ws_tuning best;
     std::memset(&best, 0, sizeof best);
     if (cache_lookup(cache_path, d->g, &best)) {
-        ws_status r = set_tuned(d, &best);
+        ws_status r = ws_set_tuning(d, &best);
         if (r == WS_OK) *out = best;
         return r;
     }
@@ -1928,7 +1916,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
     const int rows[6] = {8, 16, 24, 32, 48, 64};
     float t_rows[2][6];
     for (int c = 0; c < 6; ++c) t_rows[0][c] = t_rows[1][c] = 1e30f;
-    auto trial = [&](int c) { return height(rows[c], ROWS_TUNER, short_rows(d->g.nx, d->g.ny)); };
+    auto trial = [&](int c) { return height(rows[c], short_rows(d->g.nx, d->g.ny)); };
     for (int c = 0; c < 6; ++c) {  // warm-up
         launch_stencil(d, trial(c), st, sp);
         launch_stencil(d, trial(c), st, sa);
@@ -2018,7 +2006,7 @@ extern "C" ws_status ws_tune(ws_domain *d, const char *cache_path, void *stream,
             std::fclose(f);
         }
     }
-    ws_status r = set_tuned(d, &best);
+    ws_status r = ws_set_tuning(d, &best);
     if (r == WS_OK) *out = best;
     return r;
 }
@@ -2051,7 +2039,6 @@ extern "C" ws_status ws_batch_tune(ws_batch *b, void *stream, ws_tuning *out) {
     float best = 1e30f, best_c = 1e30f, tp[6], tc[6];
     for (int c = 0; c < 6; ++c) tp[c] = tc[c] = 1e30f;
     b->syc = 0;
-    b->rows_by = ROWS_TUNER;  // (the 8-row trial runs the rule's height)
     for (int c = 0; c < 6; ++c) {
         b->sy = rows[c];
         b->dirty = true;

@@ -17,7 +17,7 @@ constexpr int MX = 16;        // row segment length (4 per solver tile row)
 constexpr int NT = 256;       // threads per solver tile workgroup (4 wave64)
 constexpr int NTB = 128;      // the same in the batch (2 wave64)
 constexpr int SO = 62;        // stencil: output columns per 64-lane strip wave
-constexpr int SY = 32;        // stencil: rows streamed per strip wave
+constexpr int SY = 8;         // stencil: nominal rows streamed per strip wave (default)
 constexpr int SWG = 4;        // stencil: strip waves per workgroup
 constexpr int MAXC = 256;     // wave components per side
 constexpr int TABW = 8;       // doubles per component: a, omega, kx, ky, cx, cy, phase, -

@@ -199,3 +199,39 @@ def test_terrain_edit_leaves_nothing_beyond_the_rows(ny, batched):
     for x, y in zip(a.state_numpy(), t.state_numpy()):
         assert np.isfinite(x).all() and np.abs(x - y).max() <= 1e-6 * max(1.0, np.abs(y).max())
     assert a.query()[2] == 0
+
+
+def test_a_tuned_choice_can_be_set_again():
+    """What the autotuner and tuning() return, set again on the same or
+    another domain, runs what it ran: the same bits, and no slower (twice as
+    slow at 128 x 64 cells when a returned 8 set the strips to 8 rows and a
+    default of 32 to 32)."""
+    import time
+
+    import torch
+    from paper_1611_05984_amd import wavestep as ws
+
+    def us(d):
+        best = 1e9
+        for _ in range(7):
+            torch.cuda.synchronize()
+            t = time.perf_counter()
+            d.advance(150)
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t) / 150 * 1e6)
+        return best
+
+    d = [_domain(128, 64) for _ in range(4)]
+    assert d[0].tuning() == (8, 128, ws.SOLVE_PCR, 0)
+    d[1].set_tuning(*d[0].tuning())
+    choice = d[2].tune()
+    assert d[2].tuning() == choice
+    d[3].set_tuning(*choice)
+    for x in d:
+        x.advance(9)
+    _same(d[0], d[1])
+    _same(d[2], d[3])
+    t = [us(x) for x in d]
+    print("  us a step: fresh %.1f, its tuning set %.1f; tuned %s %.1f, its choice set %.1f"
+          % (t[0], t[1], choice, t[2], t[3]), flush=True)
+    assert t[1] <= 1.4 * t[0] and t[3] <= 1.4 * t[2]
