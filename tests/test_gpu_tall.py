@@ -58,3 +58,38 @@ def test_tall_forms(nx, ny, maker, sponge):
         _near(g, t)
         _equal(g, b)
     B.close()
+
+
+# reduced systems of 514, 1126 and 2048 unknowns: both register counts of every thread count
+@pytest.mark.parametrize("nx,ny,maker,sponge", [(20, 4100, 0, 3), (70, 9000, 3, 1), (20, 16384, 2, 0)])
+def test_pcr_beyond_4096_rows(nx, ny, maker, sponge):
+    """The PCR kernel of the grids past the one-kernel solve: the same bits at
+    every thread count, alone and in a batch beside a domain on the
+    one-kernel path, and the Thomas path's result."""
+    from paper_1611_05984_amd import wavestep as ws
+    print("case: pcr %dx%d maker %s sponge %s" % (nx, ny, maker, sponge), flush=True)
+    t = _domain(nx, ny, maker, sponge)
+    t.set_tuning(16, 128, ws.SOLVE_THOMAS)
+    t.advance(5)
+    alone = []
+    for threads in (64, 128, 256):
+        d = _domain(nx, ny, maker, sponge)
+        d.set_tuning(16, threads, ws.SOLVE_PCR)
+        d.advance(5)
+        alone.append(d)
+    _near(alone[0], t)
+    _equal(alone[0], alone[1])
+    _equal(alone[0], alone[2])
+    small = _domain(130, 90, 0, 1)
+    small.advance(5)
+    for threads in (64, 128, 256):
+        b, s = _domain(nx, ny, maker, sponge), _domain(130, 90, 0, 1)
+        B = ws.Batch(2)
+        B.set_tuning(16, threads, ws.SOLVE_PCR)
+        B.attach(b)
+        B.attach(s)
+        B.advance(5)
+        B.sync()
+        _equal(alone[0], b)
+        _equal(small, s)
+        B.close()
