@@ -55,10 +55,12 @@ TUNING_CACHE = os.path.join(ROOT, "paper_1611_05984_amd", "tuning_cache.txt")
 #              factors, write the solutions: 0.25 + 0.75 + 0.25
 #   expand:    reads dU*, dV* (2), P^n, Q^n, eta, depth, end values;
 #              writes P, Q                                  -> 6.25 + 2
-def alg_words(solver):
-    one = solver in (0, 4)
+#              (past 4096 rows of cells they are kernels of their own: the PCR kernel
+#              reads the equations, writes the solutions: 1 + 0.25)
+def alg_words(solver, ny=4096):
+    one = solver in (0, 4) and ny <= 4096
     reduce_w = 0.0 if one else 3.25 if solver in (2, 3) else 4.0
-    solve_w = {0: 10.0, 1: 2.25, 2: 1.25, 3: 1.25, 4: 10.0}[solver]
+    solve_w = 10.0 if one else {0: 1.25, 1: 2.25, 2: 1.25, 3: 1.25, 4: 1.25}[solver]
     return {"k_stencil[predictor]": 23.0, "k_stencil[corrector]": 10.0,
             "k_reduce": reduce_w, "reduced_solve": solve_w, "k_expand": 0.0 if one else 8.25}
 
@@ -208,7 +210,8 @@ def _timed(torch, fn, steps):
 def batched_vs_plain(args, torch, ws, wl):
     """Ensemble of 256 uneven domains: batched stepping (one launch per phase
     for all domains, one graph replay per step) against per-domain stepping
-    with the single-domain kernels on one stream, eager and graph-captured."""
+    with the single-domain kernels on one stream, eager and graph-captured,
+    every domain at the strip heights the library picks for it alone."""
     ens = wl.config4()
     cells = sum(w.cells for w in ens)
     doms = [_make(ws, w) for w in ens]
@@ -222,8 +225,8 @@ def batched_vs_plain(args, torch, ws, wl):
     n = args.ens_steps
     t_b = _timed(torch, lambda k: (B.advance(k), B.sync()), n)
     B.close()                          # domains usable alone again
-    for d in doms:                     # same launch shapes for the per-domain runs
-        d.set_tuning(*tuning)
+    for d in doms:                     # the same solve strategy, its own strip heights (8: the library's rule)
+        d.set_tuning(8, tuning[1], tuning[2])
     st = torch.cuda.Stream()
     with torch.cuda.stream(st):
         for d in doms:
@@ -299,14 +302,22 @@ def k_variants(args, torch, ws, wl):
 
 
 # kernel class (as the library's event profiler reports it) -> the symbol the
-# profiler's kernel trace shows for the tuned launch shape
-# (of a grid large enough for 8-row strips; a smaller one runs 1- or 2-row
-# kernels at a nominal 8, and k_solve_big from 1025 rows of cells on)
-def kernel_symbol(cls, tuning):
+# profiler's kernel trace shows for the tuned launch shape of an nx x ny grid:
+# a nominal 8 rows are 1 or 2 on grids of few strips (of 62 columns), the PCR
+# strategies one kernel of a form by the grid's size up to 4096 rows of cells,
+# the factored solve a lane per system past 512 unknowns (4096 cells)
+def kernel_symbol(cls, tuning, nx, ny):
     rows, _, solver, crows = tuning
-    return {"k_stencil[predictor]": "k_stencil_p<%d>" % rows,
-            "k_stencil[corrector]": "k_stencil_c<%d>" % (crows or rows),
-            "reduced_solve": ("k_solve", "k_thomas", "k_luw_solve", "k_lu2_solve", "k_solve")[solver]}.get(cls, cls)
+    strips = -(-nx // 62)
+    short = 1 if strips * ny <= 4096 else 2 if strips * -(-ny // 2) <= 72000 else 8
+    height = {8: short}
+    pcr = ("k_pcr" if ny > 4096 else "k_solve_tall" if ny > 2048 and nx <= 512 else
+           "k_solve_rows + k_solve_cols" if ny > 2048 else
+           "k_solve" if ny <= 1024 and nx <= 8192 else "k_solve_big")
+    lu = "k_luw_solve" if max(nx, ny) <= 4096 else "k_lu_solve"
+    return {"k_stencil[predictor]": "k_stencil_p<%d>" % height.get(rows, rows),
+            "k_stencil[corrector]": "k_stencil_c<%d>" % height.get(crows or rows, crows or rows),
+            "reduced_solve": (pcr, "k_thomas", lu, "k_lu2_solve", pcr)[solver]}.get(cls, cls)
 
 
 def main():
@@ -361,8 +372,8 @@ def main():
     prof = D.profile_collect()
     D.profile(False)
     tot = sum(ms for ms, n in prof.values())
-    ALG_WORDS = alg_words(tuning[2])
-    kernels = {k: {"symbol": kernel_symbol(k, tuning), "ms_avg": (ms / n if n else 0.0), "launches": n,
+    ALG_WORDS = alg_words(tuning[2], w.ny)
+    kernels = {k: {"symbol": kernel_symbol(k, tuning, w.nx, w.ny), "ms_avg": (ms / n if n else 0.0), "launches": n,
                    "share": (ms / tot if tot else 0.0), "alg_bytes_per_cell": ALG_WORDS[k] * 4,
                    "alg_GBs": (ALG_WORDS[k] * 4 * cells / (ms / n / 1e3) / 1e9 if n else 0.0)}
                for k, (ms, n) in prof.items()}

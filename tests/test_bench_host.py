@@ -35,3 +35,17 @@ def test_more_than_one_gpu_is_refused_before_any_device_work():
     assert r.returncode == 2
     assert "one GPU only" in r.stderr
     assert r.stdout == ""
+
+
+@pytest.mark.parametrize("nx,ny,tuning,want", [
+    (4096, 4096, (8, 256, 2, 0), ("k_stencil_p<8>", "k_stencil_c<8>", "k_luw_solve")),
+    (4096, 4096, (24, 128, 0, 16), ("k_stencil_p<24>", "k_stencil_c<16>", "k_solve_rows + k_solve_cols")),
+    (128, 64, (8, 128, 0, 0), ("k_stencil_p<1>", "k_stencil_c<1>", "k_solve")),
+    (2048, 2048, (8, 128, 4, 16), ("k_stencil_p<2>", "k_stencil_c<16>", "k_solve_big")),
+    (48, 4096, (8, 128, 0, 0), ("k_stencil_p<1>", "k_stencil_c<1>", "k_solve_tall")),
+    (20, 5000, (16, 64, 2, 0), ("k_stencil_p<16>", "k_stencil_c<16>", "k_lu_solve")),
+])
+def test_kernel_names_follow_the_launch_rules(nx, ny, tuning, want):
+    classes = ("k_stencil[predictor]", "k_stencil[corrector]", "reduced_solve")
+    assert tuple(bench.kernel_symbol(c, tuning, nx, ny) for c in classes) == want
+    assert bench.kernel_symbol("k_expand", tuning, nx, ny) == "k_expand"
