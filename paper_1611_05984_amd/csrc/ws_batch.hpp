@@ -220,7 +220,11 @@ __global__ __launch_bounds__(1024) void kb_solve_big(const BatchDesc *__restrict
     kb_solve_body<false>(descs, states, prefix, ndom, p, fs_buf);
 }
 
-// The same where some domain's columns are tall.
+// The same where some domain's columns are tall (128 registers, 6 spilled): every
+// domain of such a batch runs it, and still faster than as three kernels.  us
+// a step, 16-row strips, three kernels / this: 16 domains of 512 x 512 and one of
+// 256 x 2500 614 / 537, 8 of 1024 x 1024 and 64 x 4096 905 / 823, 48 of 128 x 64 and 64
+// x 2100 252 / 207, 6 of 500 x 3000 958 / 856, 4 of 700 x 700 and 2048 x 4096 1026 / 910.
 __global__ __launch_bounds__(1024) void kb_solve_tall(const BatchDesc *__restrict__ descs,
                                                       const BatchState *__restrict__ states,
                                                       const int *__restrict__ prefix, int ndom, int p) {

@@ -17,11 +17,13 @@
 // owning lanes through LDS (segments padded to FMP floats: conflict-free
 // 16-byte accesses); column workgroups read C consecutive columns of each
 // row, C lanes a run, straight into the owning lanes' registers.
-// us a pass's solves, three kernels (reduction, best PCR, expansion) / one:
-// 128 x 64 cells 17.5 / 9.5, 1024 x 512 20 / 11.8, 1024 x 1024 25 / 15.3, 2048 x
-// 1500 58 / 38.  Bound by latency up to about a million cells (4 us of launch,
-// two trips to memory), above by the columns' 32-byte runs: a workgroup pulls
-// whole 128-byte lines through its CU's 64 bytes a clock.
+// us a pass's solves, summed kernel durations of a trace, three kernels
+// (reduction, best PCR, expansion) / one: 128 x 64 cells 16.2 / 7.2, 1024 x 512
+// 18.1 / 9.1, 1024 x 1024 23.7 / 12.5, 2048 x 1500 55.8 / 35.9 (events around a
+// launch read 2 to 3 us more; the other figures in this file are such).  Bound
+// by latency up to about a million cells (two trips to memory, the reduction's
+// levels), above by the columns' 32-byte runs: a workgroup pulls whole 128-byte
+// lines through its CU's 64 bytes a clock.
 #pragma once
 #include "ws_kernels.hpp"
 
@@ -461,8 +463,8 @@ __global__ __launch_bounds__(FS_EARLY) void k_solve_tall(SolveArgs A) {
     solve_body<true, true>(A, fs_buf, blockIdx.x);
 }
 // Wider grids, at 8 columns a run: columns of more than FS_TALL cells fill a
-// CU's registers with one workgroup, so the rows get a launch of their own,
-// with small workgroups.
+// CU's registers with one workgroup (128 a lane, 6 more spilled to 28 bytes of
+// scratch), so the rows get a launch of their own, with small workgroups.
 __global__ __launch_bounds__(1024) void k_solve_rows(SolveArgs A) {
     extern __shared__ __align__(16) float fs_buf[];
     solve_rows<false>(A, fs_buf, blockDim.x, xcd_order(blockIdx.x, gridDim.x));
