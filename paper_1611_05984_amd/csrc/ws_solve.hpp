@@ -85,7 +85,7 @@ constexpr size_t fs_lds(int T) { return (size_t)T * FMP * sizeof(float); }
 // ends fold as in seg_coefs (glo, ghi: the maker's discharge change, 0 behind
 // a wall), by selects: a branch had the compiler copy all the arrays.  Cells
 // past the end need not be identity rows, as no cell of the line refers to
-// them, but finite ones: the callers give them the ghost's depth.  Coefficients and forward elimination go cell by cell, with a
+// them, but finite ones: the callers give them a depth of zero or the ghost's.  Coefficients and forward elimination go cell by cell, with a
 // scheduling fence every few, so that the depths die as the rows are born.
 template <int M>
 __device__ __forceinline__ void fs_eliminate(TriK tk, int i0, int n, bool lo_wall, bool hi_wall, float glo, float ghi,
@@ -209,10 +209,11 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
         vr[m] = live ? *reinterpret_cast<const float4 *>(A.rx + o + q) : make_float4(0.f, 0.f, 0.f, 0.f);
         vd[m] = live ? *reinterpret_cast<const float4 *>(A.Dc + panel(q, jl, d.ny)) : make_float4(0.f, 0.f, 0.f, 0.f);
         // padding past the row's end is never written: whatever it holds must not spread
-        vr[m].x = q < d.nx ? vr[m].x : 0.f;
-        vr[m].y = q + 1 < d.nx ? vr[m].y : 0.f;
-        vr[m].z = q + 2 < d.nx ? vr[m].z : 0.f;
-        vr[m].w = q + 3 < d.nx ? vr[m].w : 0.f;
+        // (the depths' holds other data, old corners after a terrain edit, whose pivots
+        // can vanish)
+        const bool in0 = q < d.nx, in1 = q + 1 < d.nx, in2 = q + 2 < d.nx, in3 = q + 3 < d.nx;
+        vr[m] = make_float4(in0 ? vr[m].x : 0.f, in1 ? vr[m].y : 0.f, in2 ? vr[m].z : 0.f, in3 ? vr[m].w : 0.f);
+        vd[m] = make_float4(in0 ? vd[m].x : 0.f, in1 ? vd[m].y : 0.f, in2 ? vd[m].z : 0.f, in3 ? vd[m].w : 0.f);
     }
     const int i0 = s * FM;
     float glo = 0.f, ghi = 0.f, dlo = 0.f, dhi = 0.f;  // maker changes and ghost depths of the row's ends
@@ -258,15 +259,13 @@ __device__ __forceinline__ void solve_rows(const SolveArgs &A, float *lds, int T
         r[k + 2] = v.z;
         r[k + 3] = v.w;
     }
-    {   // the ghost past the row's last cell: mirrored, or held behind a maker; and the
-        // same for the cells after it: the field holds other data there (old
-        // corners, after a terrain edit), whose pivots can vanish
+    {   // the ghost past the row's last cell: mirrored, or held behind a maker
         const int kl = d.nx - 1 - i0;
         const bool wall = is_wall(d, 1);
 #pragma unroll
         for (int k = 0; k < FM; ++k) {
             const float gd = wall ? dep[k + 1] : dhi;
-            dep[k + 2] = k < kl ? dep[k + 2] : gd;
+            dep[k + 2] = k == kl ? gd : dep[k + 2];
         }
     }
     __syncthreads();
