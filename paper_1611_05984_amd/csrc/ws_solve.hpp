@@ -18,8 +18,8 @@
 // 16-byte accesses); column workgroups read C consecutive columns of each
 // row, C lanes a run, straight into the owning lanes' registers.
 // us a pass's solves, summed kernel durations of a trace, three kernels
-// (reduction, best PCR, expansion) / one: 128 x 64 cells 16.2 / 7.2, 1024 x 512
-// 18.1 / 9.1, 1024 x 1024 23.7 / 12.5, 2048 x 1500 55.8 / 35.9 (events around a
+// (reduction, best PCR, expansion) / one: 128 x 64 cells 16.2 / 6.8, 1024 x 512
+// 18.1 / 8.9, 1024 x 1024 23.7 / 12.9, 2048 x 1500 55.8 / 35.8 (events around a
 // launch read 2 to 3 us more; the other figures in this file are such).  Bound
 // by latency up to about a million cells (two trips to memory, the reduction's
 // levels), above by the columns' 32-byte runs: a workgroup pulls whole 128-byte
@@ -53,7 +53,7 @@ inline int fs_threads(int nx, int ny) {
 // of 4 columns a run: at 8 it gives too few workgroups, and its rows, in a
 // launch of their own, are over in a moment.  us a step of the three kernels /
 // rows and columns apart / one launch: 48 x 3000 cells 94 / 118 / 90, 48 x 4096
-// 111 / 142 / 114, 256 x 2500 129 / 138 / 104, 512 x 3000 192 / 182 / 165; 700 x 2500
+// 111 / 142 / 113, 256 x 2500 129 / 138 / 103, 512 x 3000 192 / 182 / 164; 700 x 2500
 // (rows and columns apart / one launch) 186 / 189.
 constexpr int FS_NARROW = 512;
 inline bool fs_narrow(int nx, int ny) { return ny > FS_TALL && nx <= FS_NARROW; }
